@@ -1,0 +1,310 @@
+"""Measured cases of the direct Monte Carlo parameter scan.
+
+Each case is one pass through a public entry point of the package on a scan
+(or a mix of scans) of the sizes its users run: the paper's own workloads
+(Eq. (2), Eq. (4), the Boltzmann-shaped grid of Sec. 3.3), the benchmark's
+single scans, batches and served mixes, and a user-defined integrand.
+
+A case is a dict of plain values:
+  entry      "device"  zmc.scan_device on device-resident lists and outputs
+             "host"    zmc.integrate, host arrays in and out
+             "batch"   zmc.Batch.launch on a mix of scans (one graph replay)
+             "server"  zmc.Server: submit a mix, wait for every request
+  family     sin_sum, gauss, cosexp or user (a Gaussian written as source)
+  precision  fp64 or fp32 (FP32 evaluation, FP64 merge)
+  grid       values per parameter, e.g. "1000x1000"
+  dims       integration dimensions N
+  samples    samples per grid point n
+  box        edge of the integration box (sin_sum)
+  scans, shape_seed, points, samples   (batch, server) the mix: scan i's
+             family, N in 2..8, grid size log-uniform up to `points` and n up
+             to `samples` come from shape_seed; its values from the pass's seed
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_1910_01965_amd import workloads as wl
+from paper_1910_01965_amd import zmc
+
+USER_GAUSS = """
+template <typename T> __device__ T integrand(const T* y, const T* x, const T* p) {
+  return p[0] * exp(-(x[0] * y[0] * y[0] + x[1] * y[1] * y[1] + y[2] * y[2]));
+}
+"""
+USER_SCALE = 1.25  # the constant p[0] of USER_GAUSS
+
+
+def listed():
+    return [
+        # the paper's smallest Table 1 cell (M = N = 1): 100 points, 10^4 samples,
+        # box [0, 10]; launches and latency are most of it
+        dict(name="table1_smallest_fp64", entry="device", family="sin_sum", precision="fp64",
+             grid="100", dims=1, samples=10000, box=10.0),
+        # a small exploratory scan as a script writes it: host lists in, host
+        # arrays out, ragged grid and an odd sample count
+        dict(name="integrate_small_host_fp64", entry="host", family="gauss", precision="fp64",
+             grid="37x41", dims=3, samples=4099, box=1.0),
+        # the plain FP64 scan of the benchmark: 1000 points, 2^16 samples, N = 4
+        dict(name="plain_fp64_1000", entry="device", family="sin_sum", precision="fp64",
+             grid="1000", dims=4, samples=65536, box=1.0),
+        # the headline scan: 10^6-point Gaussian grid, 2^14 samples, FP32 evaluation
+        dict(name="gauss_2p_fp32", entry="device", family="gauss", precision="fp32",
+             grid="1000x1000", dims=3, samples=16384, box=1.0),
+        # the same grid in full FP64
+        dict(name="gauss_2p_fp64", entry="device", family="gauss", precision="fp64",
+             grid="1000x1000", dims=3, samples=16384, box=1.0),
+        # the largest single scan: 10^8 points over four parameters, FP32
+        dict(name="cosexp_4p_1e8_fp32", entry="device", family="cosexp", precision="fp32",
+             grid="100x100x100x100", dims=2, samples=4096, box=1.0),
+        # the four-parameter scan in FP64 on a coarser, odd grid
+        dict(name="cosexp_4p_odd_fp64", entry="device", family="cosexp", precision="fp64",
+             grid="31x31x31x31", dims=2, samples=4093, box=1.0),
+        # a very large grid with a handful of samples per point, as the
+        # out-of-core grids are run: set-up and output per point matter
+        dict(name="large_grid_16_samples_fp32", entry="device", family="sin_sum", precision="fp32",
+             grid="1000x100x100", dims=2, samples=16, box=1.0),
+        # a mid-sized grid in many integration dimensions
+        dict(name="wide_n12_fp64", entry="device", family="sin_sum", precision="fp64",
+             grid="211x97", dims=12, samples=2049, box=1.0),
+        # many uneven scans in one graph
+        dict(name="batch_mix_fp32", entry="batch", precision="fp32", scans=48, shape_seed=3,
+             points=100000, samples=32768),
+        # requests of both precisions through the server's request loop
+        dict(name="server_mix", entry="server", precision="both", scans=24, shape_seed=11,
+             points=30000, samples=16384),
+        # a user-defined integrand, as the paper's users write theirs
+        dict(name="user_gauss_fp32", entry="device", family="user", precision="fp32",
+             grid="300x301", dims=3, samples=8192, box=1.0),
+    ]
+
+
+_DRAW_LIMIT = 2e11  # samples x N of a drawn case (the largest listed one has 8.2e11)
+
+
+def draw(rng):
+    entry = rng.choice(["device"] * 7 + ["host", "batch", "server"])
+    precision = rng.choice(["fp64", "fp32"])
+    if entry in ("batch", "server"):
+        return dict(entry=entry, precision=rng.choice([precision, "both"]) if entry == "server" else precision,
+                    scans=rng.randint(8, 48), shape_seed=rng.randint(100, 10 ** 6),
+                    points=int(10 ** rng.uniform(3.5, 5.0)), samples=int(2 ** rng.uniform(11, 15)))
+    family = rng.choice(["sin_sum", "gauss", "cosexp", "sin_sum", "gauss", "cosexp", "user"])
+    if entry == "host" and family == "user":
+        family = "gauss"
+    dims = 3 if family == "user" else rng.choice([rng.randint(2, 8)] * 3 + [rng.randint(9, 16)])
+    if family == "sin_sum" and rng.random() < 0.2:
+        dims = 1
+    m = {"gauss": rng.randint(1, min(dims, 3)), "cosexp": 4, "user": 2}.get(family) or rng.randint(1, 5)
+    top = 5.0 if entry == "host" else 7.0
+    axis = 10 ** (rng.uniform(math.log10(50), top) / m)
+    lens = [max(2, int(round(axis * rng.uniform(0.8, 1.25)))) for _ in range(m)]
+    G = math.prod(lens)
+    most = max(16.0, min(2.0 ** 17, _DRAW_LIMIT / (G * dims)))
+    samples = int(2 ** rng.uniform(4, math.log2(most)))
+    if rng.random() < 0.5:
+        samples |= 1
+    return dict(entry=entry, family=family, precision=precision, grid="x".join(map(str, lens)),
+                dims=dims, samples=max(2, samples), box=rng.choice([1.0, 1.0, 10.0]) if family == "sin_sum" else 1.0)
+
+
+# ------------------------------------------------------------------ inputs --
+def _scan_spec(family, precision, lens, dims, samples, box, rng):
+    """One scan: value lists, box and Philox seed drawn from `rng` in the
+    ranges of the repository's workloads."""
+    lo, hi = np.zeros(dims), np.full(dims, box)
+    extra = {}
+    if family == "sin_sum":
+        axes = []
+        for L in lens:
+            a = rng.uniform(0.0, 0.3)
+            axes.append(np.linspace(a, a + box * rng.uniform(0.7, 1.3), L))
+    elif family in ("gauss", "user"):
+        axes = [np.linspace(0.1 * rng.uniform(0.5, 2.0), 10.0 * rng.uniform(0.7, 1.0), L) for L in lens]
+    else:
+        axes = [np.linspace(-rng.uniform(0.8, 1.0), rng.uniform(0.8, 1.0), L) for L in lens]
+        hi[0] = 2.0
+    if family == "user":
+        extra = dict(source=USER_GAUSS, params=np.array([USER_SCALE]))
+    return wl.ScanSpec(family, axes, lo, hi, samples, int(rng.integers(0, 2 ** 62)), precision, **extra)
+
+
+def _specs(case, seed):
+    rng = np.random.default_rng([int(seed), 1910])
+    if case["entry"] in ("batch", "server"):
+        shape = np.random.default_rng(case["shape_seed"])
+        out = []
+        for i in range(case["scans"]):
+            family = ("sin_sum", "gauss", "cosexp")[int(shape.integers(0, 3))]
+            dims = int(shape.integers(2, 9))
+            target = math.exp(shape.uniform(math.log(300.0), math.log(case["points"])))
+            m = {"sin_sum": 1, "gauss": 2, "cosexp": 4}[family]
+            L = max(2, int(round(target ** (1.0 / m))))
+            samples = int(2 ** shape.uniform(8, math.log2(case["samples"])))
+            precision = ("fp32", "fp64")[i % 2] if case["precision"] == "both" else case["precision"]
+            out.append(_scan_spec(family, precision, [L] * m, dims, samples, 1.0, rng))
+        return out
+    lens = [int(v) for v in case["grid"].split("x")]
+    return [_scan_spec(case["family"], case["precision"], lens, case["dims"], case["samples"],
+                       case["box"], rng)]
+
+
+def _outputs(spec):
+    return (torch.empty(spec.G, dtype=torch.float64, device="cuda"),
+            torch.empty(spec.G, dtype=torch.float64, device="cuda"))
+
+
+def prepare(case, seed):
+    specs = _specs(case, seed)
+    state = dict(entry=case["entry"], specs=specs)
+    if case["entry"] == "host":
+        sp = specs[0]
+        state.update(domain=list(zip(sp.lo.tolist(), sp.hi.tolist())), parameters=sp.axes)
+        return state
+    state["axes"] = [zmc.axis_tensor(sp) for sp in specs]
+    state["outputs"] = [_outputs(sp) for sp in specs]
+    if case["entry"] == "batch":
+        state["batch"] = zmc.Batch(specs, outputs=state["outputs"], axes=state["axes"])
+    elif case["entry"] == "server":
+        state["server"] = zmc.Server()
+    return state
+
+
+def run(state):
+    entry, specs = state["entry"], state["specs"]
+    if entry == "host":
+        sp = specs[0]
+        return zmc.integrate(sp.family, state["domain"], state["parameters"], sp.samples,
+                             seed=sp.seed, precision=sp.precision)
+    if entry == "batch":
+        state["batch"].launch()
+        return state["outputs"]
+    if entry == "server":
+        server = state["server"]
+        tickets = [server.submit(sp, f=f, sigma=s, axis=a)
+                   for sp, (f, s), a in zip(specs, state["outputs"], state["axes"])]
+        for t in tickets:
+            status, _ = server.wait(t)
+            if status != 0:
+                raise RuntimeError("request %d finished with status %d" % (t, status))
+        return [server.outputs(t) for t in tickets]
+    f, s = state["outputs"][0]
+    zmc.scan_device(specs[0], state["axes"][0], f, s)
+    return f, s
+
+
+def _spec_sizes(case):
+    """(G, n, N, M values, family) of each scan of a case."""
+    return [(sp.G, sp.samples, sp.N, sum(sp.shape), sp.family) for sp in _specs(case, 0)]
+
+
+def work(case):
+    """Lists read and f, sigma written once; the method's operations per
+    sample: 10 N of the generator, 2 N of the map into the box, the integrand's
+    and 8 of the sums."""
+    own = {"sin_sum": lambda N: N + 1, "gauss": lambda N: 2 * N + 1, "user": lambda N: 2 * N + 1,
+           "cosexp": lambda N: N + 5}
+    total, ops = 0, 0
+    for G, n, N, values, family in _spec_sizes(case):
+        total += 8 * values + 16 * G
+        ops += G * n * (12 * N + own[family](N) + 8)
+    return {"bytes": total, "flops": ops}
+
+
+# ------------------------------------------------- the results in 64 bits --
+_M0, _M1, _W0, _W1, _MASK = 0xD2511F53, 0xCD9E8D57, 0x9E3779B9, 0xBB67AE85, 0xFFFFFFFF
+_EXACT_WORDS = 6e10 if torch.cuda.is_available() else 2e8  # about 20 seconds
+
+
+def _philox(c0, c1, c2, c3, seed):
+    """Philox4x32-10 on int64 tensors holding 32-bit words (Salmon et al., SC'11);
+    products wrap to their low 64 bits, which hold both halves."""
+    k0, k1 = seed & _MASK, (seed >> 32) & _MASK
+    for _ in range(10):
+        p0 = c0 * _M0
+        p1 = c2 * _M1
+        c0 = (p1 >> 32).bitwise_and_(_MASK).bitwise_xor_(c1).bitwise_xor_(k0)
+        c2 = (p0 >> 32).bitwise_and_(_MASK).bitwise_xor_(c3).bitwise_xor_(k1)
+        c1 = p1.bitwise_and_(_MASK)
+        c3 = p0.bitwise_and_(_MASK)
+        k0, k1 = (k0 + _W0) & _MASK, (k1 + _W1) & _MASK
+    return c0, c1, c2, c3
+
+
+def _value(sp, x, y):
+    """g(y; x): x a list of M columns [P, 1], y a list of N [P, S] tensors."""
+    if sp.family == "sin_sum":
+        ph = sum(x)
+        for v in y:
+            ph = ph + v
+        return torch.sin(ph)
+    if sp.family in ("gauss", "user"):
+        q = 0.0
+        for k, v in enumerate(y):
+            q = q + (x[k] * v * v if k < len(x) else v * v)
+        g = torch.exp(-q)
+        return USER_SCALE * g if sp.family == "user" else g
+    ph = x[0] * y[0] + x[1] * y[1]
+    for v in y[2:]:
+        ph = ph + v
+    return torch.cos(ph) * torch.exp(-x[2] * x[2] * y[0] * y[1]) + x[3]
+
+
+def _exact_scan(sp, dev):
+    G, n, N = sp.G, sp.samples, sp.N
+    idx = torch.arange(G, dtype=torch.int64, device=dev)
+    cols, stride = [], G
+    for a in sp.axes:
+        stride //= len(a)
+        cols.append(torch.from_numpy(a).to(dev)[torch.div(idx, stride, rounding_mode="floor") % len(a)])
+    groups = (n + 3) // 4
+    tile = 1 << 22 if dev == "cuda" else 1 << 18  # Philox blocks at a time
+    step_g = max(1, min(groups, tile // N))
+    step_p = max(1, min(G, tile // (step_g * N)))
+    vol = float(np.prod(sp.hi - sp.lo))
+    f = torch.empty(G, dtype=torch.float64, device=dev)
+    sigma = torch.empty(G, dtype=torch.float64, device=dev)
+    for p0 in range(0, G, step_p):
+        p1 = min(G, p0 + step_p)
+        g = idx[p0:p1, None]
+        x = [c[p0:p1, None] for c in cols]
+        count, mean, m2 = 0, 0.0, 0.0
+        for j0 in range(0, groups, step_g):
+            j1 = min(groups, j0 + step_g)
+            b = torch.arange(j0 * N, j1 * N, dtype=torch.int64, device=dev)[None, :]
+            shape = (p1 - p0, b.shape[1])
+            words = _philox((b & _MASK).expand(shape), (b >> 32).expand(shape),
+                            (g & _MASK).expand(shape), (g >> 32).expand(shape), sp.seed)
+            s1 = min(n, 4 * j1) - 4 * j0
+            w = torch.stack(words, dim=2).reshape(p1 - p0, -1, N)[:, :s1]
+            del words
+            if sp.precision == "fp64":
+                u = (w.double() + 0.5) * 2.0 ** -32
+            else:
+                u = ((w >> 9).double() + 0.5) * 2.0 ** -23
+            del w
+            y = [sp.lo[k] + (sp.hi[k] - sp.lo[k]) * u[:, :, k] for k in range(N)]
+            v = _value(sp, x, y)
+            del u, y
+            tm = v.mean(dim=1)
+            t2 = (v - tm[:, None]).square_().sum(dim=1)
+            d = tm - mean
+            m2 = m2 + t2 + d * d * (count * s1 / (count + s1))
+            mean = mean + d * (s1 / (count + s1))
+            count += s1
+        f[p0:p1] = vol * mean
+        sigma[p0:p1] = vol * torch.sqrt(m2 / (n * (n - 1.0)))
+    return f, sigma
+
+
+def exact(case, seed):
+    specs = _specs(case, seed)
+    if sum(sp.G * sp.samples * sp.N for sp in specs) > _EXACT_WORDS:
+        return None
+    dev = "cuda" if torch.cuda.is_available() else "cpu"
+    got = [_exact_scan(sp, dev) for sp in specs]
+    if case["entry"] == "host":
+        shape = specs[0].shape
+        return tuple(v.cpu().numpy().reshape(shape) for v in got[0])
+    return got if case["entry"] in ("batch", "server") else got[0]
