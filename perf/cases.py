@@ -69,7 +69,7 @@ def listed():
         dict(name="wide_n12_fp64", entry="device", family="sin_sum", precision="fp64",
              grid="211x97", dims=12, samples=2049, box=1.0),
         # many uneven scans in one graph
-        dict(name="batch_mix_fp32", entry="batch", precision="fp32", scans=48, shape_seed=3,
+        dict(name="batch_mix_fp32", entry="batch", precision="fp32", scans=30, shape_seed=3,
              points=100000, samples=32768),
         # requests of both precisions through the server's request loop
         dict(name="server_mix", entry="server", precision="both", scans=24, shape_seed=11,
@@ -88,7 +88,7 @@ def draw(rng):
     precision = rng.choice(["fp64", "fp32"])
     if entry in ("batch", "server"):
         return dict(entry=entry, precision=rng.choice([precision, "both"]) if entry == "server" else precision,
-                    scans=rng.randint(8, 48), shape_seed=rng.randint(100, 10 ** 6),
+                    scans=rng.randint(8, 30), shape_seed=rng.randint(100, 10 ** 6),
                     points=int(10 ** rng.uniform(3.5, 5.0)), samples=int(2 ** rng.uniform(11, 15)))
     family = rng.choice(["sin_sum", "gauss", "cosexp", "sin_sum", "gauss", "cosexp", "user"])
     if entry == "host" and family == "user":
