@@ -121,6 +121,68 @@ __host__ __device__ __forceinline__ Words4 philox_block(uint64_t b, uint64_t g, 
 }
 
 // ---------------------------------------------------------------------------
+// Issue phases.  A CU's SIMD issues one wave64 VALU instruction every four
+// cycles (a slot), or two from different waves when both are of the pairing
+// kind.  Measured on the MI355X (loops of one or two instruction forms, 4 to 8
+// waves per SIMD, cycles per instruction):
+//   xor, and, shift, 32-bit add, bitop3, FP32 add/mul/fma    2.1 (pairs)
+//   the same with an SGPR operand                            4.1 (of a pair, only
+//                                                            one may read an SGPR)
+//   v_mad_u64_u32, v_alignbit, conversions, FP64             4.1 (v_mad_u64_u32
+//                                                            pairs with FP32 only)
+//   v_exp_f32, v_sin_f32                                     8.2
+// Philox alternates the two kinds: two wide products, then two three-way xors
+// per round.  Left alone the waves drift apart, the xors of one meet the
+// products of the others, and nothing pairs (4.1 cycles per instruction over a
+// whole block).  So the wave priority is raised for the products and for the
+// floating-point work of a group and lowered for the xors: a wave that reaches
+// its xors waits there until the others have reached theirs, and the xors
+// issue in pairs (3.1 per instruction, 297 cycles for three blocks instead of
+// 393).  For this the round keys live in vector registers.
+// The phases are empty asm statements through which the phase's values pass,
+// so that data flow alone keeps the order and unused blocks still vanish.
+// Effect (kernel times, start -> here): Gaussian 10^6 points x 4096 samples,
+// N = 3, FP32 3.53 -> 2.97 ms, FP64 6.19 -> 5.68 ms; COSEXP 32^4 points x 4096,
+// N = 2, FP32 3.12 -> 2.72 ms, FP64 6.99 -> 6.75 ms.
+// ---------------------------------------------------------------------------
+
+// Blocks whose phases run together: enough xors at a time to pair well, few
+// enough values to keep five FP32 waves per SIMD (1, 2, 3, 4 blocks: 3.13,
+// 3.06, 3.03, 3.04 ms for the FP32 Gaussian above).
+constexpr int kMaxBatch = 3;
+constexpr int kKeyRounds = 7;  // rounds 4..10, whose keys are kept in VGPRs
+
+// x in a vector register (a wave-uniform value would go to an SGPR).
+template <typename T> __host__ __device__ __forceinline__ T in_vgpr(T x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+v"(x));
+#endif
+  return x;
+}
+
+#if defined(__HIP_DEVICE_COMPILE__)
+#define ZMC_PHASE(NAME, T, PRIO)                                                              \
+  template <int NB>                                                                           \
+  __device__ __forceinline__ void NAME(T (&a)[NB], T (&b)[NB]) {                              \
+    static_assert(NB >= 1 && NB <= kMaxBatch, "phases of one to three blocks");               \
+    if constexpr (NB == 1)                                                                    \
+      asm("s_setprio " PRIO : "+v"(a[0]), "+v"(b[0]));                                        \
+    else if constexpr (NB == 2)                                                               \
+      asm("s_setprio " PRIO : "+v"(a[0]), "+v"(b[0]), "+v"(a[1]), "+v"(b[1]));                \
+    else                                                                                      \
+      asm("s_setprio " PRIO                                                                   \
+          : "+v"(a[0]), "+v"(b[0]), "+v"(a[1]), "+v"(b[1]), "+v"(a[2]), "+v"(b[2]));          \
+  }
+#else
+#define ZMC_PHASE(NAME, T, PRIO) \
+  template <int NB> __host__ __device__ inline void NAME(T (&)[NB], T (&)[NB]) {}
+#endif
+ZMC_PHASE(phase_mul, uint32_t, "2")
+ZMC_PHASE(phase_int, uint64_t, "0")
+ZMC_PHASE(phase_float, uint32_t, "3")
+#undef ZMC_PHASE
+
+// ---------------------------------------------------------------------------
 // The same blocks for the point-major layout when b < 2^32 and g < 2^32 (the
 // host checks both for the whole scan).  All lanes of a wave then share b and
 // differ in g only, so the first two rounds split into a per-lane part that
@@ -187,6 +249,87 @@ __host__ __device__ __forceinline__ Words4 philox_block_pm(uint32_t b, const Phi
   Words4 w;
   w.r[0] = c0; w.r[1] = c1; w.r[2] = c2; w.r[3] = c3;
   return w;
+}
+
+// The same with what the issue phases need.
+struct PhiloxPhasedLane {
+  PhiloxLane L;
+  uint32_t l2k;                 // l2 ^ round 3's second key
+  uint32_t kv[2 * kKeyRounds];  // keys of rounds 4..10, in vector registers
+};
+
+__host__ __device__ __forceinline__ PhiloxPhasedLane philox_phased_lane(uint32_t g, uint64_t seed) {
+  PhiloxPhasedLane P;
+  P.L = philox_lane(g, seed);
+  P.l2k = P.L.l2 ^ (P.L.k1 + 2 * kPhiloxW1);
+#pragma unroll
+  for (int i = 0; i < kKeyRounds; ++i) {
+    P.kv[2 * i] = in_vgpr(P.L.k0 + (uint32_t)(3 + i) * kPhiloxW0);
+    P.kv[2 * i + 1] = in_vgpr(P.L.k1 + (uint32_t)(3 + i) * kPhiloxW1);
+  }
+  return P;
+}
+
+// Blocks b0 .. b0 + NB - 1 of the lane's grid point, NB <= kMaxBatch.
+template <int NB>
+__host__ __device__ __forceinline__ void philox_blocks_pm(uint32_t b0, const PhiloxPhasedLane& P,
+                                                             Words4 w[NB]) {
+  const PhiloxLane& L = P.L;
+  uint32_t c0[NB], c2[NB], u1[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const uint32_t b = b0 + (uint32_t)i;
+    // round 1 (key k): words 0, 1 per lane and fixed; words 2, 3 uniform
+    const uint64_t q0 = (uint64_t)kPhiloxM0 * b;
+    const uint32_t u2 = (uint32_t)(q0 >> 32) ^ L.k1;  // counter word 3 (g hi) is 0
+    const uint32_t u3 = (uint32_t)q0;
+    // round 2 (key k + W): the product with word 2 is uniform
+    const uint32_t k0b = L.k0 + kPhiloxW0, k1b = L.k1 + kPhiloxW1;
+    const uint64_t q1 = (uint64_t)kPhiloxM1 * u2;
+    c0[i] = L.r1 ^ ((uint32_t)(q1 >> 32) ^ k0b);
+    c2[i] = L.h2 ^ (u3 ^ k1b);
+    u1[i] = (uint32_t)q1 ^ (L.k0 + 2 * kPhiloxW0);
+  }
+  uint64_t p[NB], q[NB], pp[NB], qq[NB];
+  phase_mul<NB>(c0, c2);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    p[i] = (uint64_t)kPhiloxM0 * c0[i];
+    q[i] = (uint64_t)kPhiloxM1 * c2[i];
+  }
+  phase_int<NB>(p, q);
+  // round 3: word 1 and the key are uniform, word 3 is per lane and fixed,
+  // so each new word is one per-lane product high half and one xor
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    c0[i] = (uint32_t)(q[i] >> 32) ^ u1[i];
+    c2[i] = (uint32_t)(p[i] >> 32) ^ P.l2k;
+  }
+#pragma unroll
+  for (int r = 0; r < kKeyRounds; ++r) {
+    phase_mul<NB>(c0, c2);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      pp[i] = (uint64_t)kPhiloxM0 * c0[i];
+      qq[i] = (uint64_t)kPhiloxM1 * c2[i];
+    }
+    phase_int<NB>(pp, qq);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      c0[i] = xor3((uint32_t)(qq[i] >> 32), (uint32_t)q[i], P.kv[2 * r]);
+      c2[i] = xor3((uint32_t)(pp[i] >> 32), (uint32_t)p[i], P.kv[2 * r + 1]);
+      p[i] = pp[i];
+      q[i] = qq[i];
+    }
+  }
+  phase_float<NB>(c0, c2);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    w[i].r[0] = c0[i];
+    w[i].r[1] = (uint32_t)q[i];
+    w[i].r[2] = c2[i];
+    w[i].r[3] = (uint32_t)p[i];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -523,40 +666,110 @@ template <typename T, int N> struct Linear {
 struct GenAny {
   uint64_t g, seed;
   __device__ __forceinline__ Words4 block(uint64_t b) const { return philox_block(b, g, seed); }
+  template <int NB>
+  __device__ __forceinline__ void blocks(uint64_t b, Words4 w[NB]) const {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) w[i] = block(b + (uint64_t)i);
+  }
+  template <typename T> __device__ __forceinline__ GenAny after(T&) const { return *this; }
 };
 
 struct GenPointMajor {
   PhiloxLane L;
+  static __device__ __forceinline__ GenPointMajor make(uint32_t g, uint64_t seed) {
+    return {philox_lane(g, seed)};
+  }
   __device__ __forceinline__ Words4 block(uint64_t b) const {
     return philox_block_pm((uint32_t)b, L);
   }
 };
 
+struct GenPointMajorPhased {
+  PhiloxPhasedLane P;
+  static __device__ __forceinline__ GenPointMajorPhased make(uint32_t g, uint64_t seed) {
+    return {philox_phased_lane(g, seed)};
+  }
+  template <int NB>
+  __device__ __forceinline__ void blocks(uint64_t b, Words4 w[NB]) const {
+    philox_blocks_pm<NB>((uint32_t)b, P, w);
+  }
+  // the same generator, whose blocks wait for v
+  template <typename T> __device__ __forceinline__ GenPointMajorPhased after(T& v) const {
+    GenPointMajorPhased g = *this;
+    asm("" : "+v"(g.P.L.r1), "+v"(v));
+    return g;
+  }
+};
+
+// Families whose groups run in issue phases: all but those that set
+// kPhased = false (the FP32 user integrands: the order in which the compiler
+// contracts a user's own products and sums into FMAs changes with the code
+// around them, by up to 1e-8 of the result, so they keep the code they had).
+template <class Fam, class = void> struct Phased : std::true_type {};
+template <class Fam>
+struct Phased<Fam, std::void_t<decltype(Fam::kPhased)>> : std::integral_constant<bool, Fam::kPhased> {};
+
+// Word blocks drawn together (see the issue phases), in equal batches.
+template <int N>
+constexpr int kBatchBlocks = (N + (N + kMaxBatch - 1) / kMaxBatch - 1) / ((N + kMaxBatch - 1) / kMaxBatch);
+
+// Blocks C .. of the group in batches; a sample is evaluated as soon as the
+// batch that holds its last word (word sN + N - 1) has been drawn, and before
+// the next batch starts (gen.after), so that in many dimensions only the
+// variates of about one sample are live at a time.
+template <class Fam, typename T, int N, class Gen, int C = 0>
+__device__ __forceinline__ void eval_blocks(const Fam& fam, uint64_t b0, const Gen& gen, T t[4 * N],
+                                            T v[4]) {
+  if constexpr (C < N) {
+    constexpr int NB = N - C < kBatchBlocks<N> ? N - C : kBatchBlocks<N>;
+    Words4 w[NB];
+    gen.template blocks<NB>(b0 + C, w);
+#pragma unroll
+    for (int i = 0; i < 4 * NB; ++i) t[4 * C + i] = Unif<T>::t(w[i / 4].r[i % 4]);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int last = (s * N + N - 1) / 4;
+      if (last >= C && last < C + NB) v[s] = fam.value(t + s * N);
+    }
+    constexpr int done = 4 * (C + NB) / N;  // samples evaluated so far
+    if constexpr (C + NB < N && done > 0 && done > 4 * C / N) {
+      eval_blocks<Fam, T, N, Gen, C + NB>(fam, b0, gen.after(v[done - 1]), t, v);
+    } else {
+      eval_blocks<Fam, T, N, Gen, C + NB>(fam, b0, gen, t, v);
+    }
+  }
+}
+
 template <class Fam, typename T, int N, class Gen>
 __device__ __forceinline__ void eval_group(const Fam& fam, uint64_t j, const Gen& gen, T v[4]) {
-  T t[4 * N];
-  const uint64_t b0 = j * (uint64_t)N;
-  if constexpr (N <= kAnyMaxDims) {
-#pragma unroll
-    for (int c = 0; c < N; ++c) {
-      const Words4 w = gen.block(b0 + c);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) t[4 * c + i] = Unif<T>::t(w.r[i]);
-    }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) v[s] = fam.value(t + s * N);
+  if constexpr (Phased<Fam>::value) {
+    T t[4 * N];
+    eval_blocks<Fam, T, N, Gen>(fam, j * (uint64_t)N, gen, t, v);
   } else {
-    // many dimensions: sample s is evaluated right after the block that holds
-    // its last word (word sN + N - 1), so that only the variates of about one
-    // sample are live at a time; the values are the same
+    T t[4 * N];
+    const uint64_t b0 = j * (uint64_t)N;
+    if constexpr (N <= kAnyMaxDims) {
 #pragma unroll
-    for (int c = 0; c < N; ++c) {
-      const Words4 w = gen.block(b0 + c);
+      for (int c = 0; c < N; ++c) {
+        const Words4 w = gen.block(b0 + c);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) t[4 * c + i] = Unif<T>::t(w.r[i]);
+        for (int i = 0; i < 4; ++i) t[4 * c + i] = Unif<T>::t(w.r[i]);
+      }
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-        if ((s * N + N - 1) / 4 == c) v[s] = fam.value(t + s * N);
+      for (int s = 0; s < 4; ++s) v[s] = fam.value(t + s * N);
+    } else {
+      // many dimensions: sample s is evaluated right after the block that holds
+      // its last word (word sN + N - 1), so that only the variates of about one
+      // sample are live at a time; the values are the same
+#pragma unroll
+      for (int c = 0; c < N; ++c) {
+        const Words4 w = gen.block(b0 + c);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[4 * c + i] = Unif<T>::t(w.r[i]);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          if ((s * N + N - 1) / 4 == c) v[s] = fam.value(t + s * N);
+      }
     }
   }
 }

@@ -74,7 +74,8 @@ __device__ __forceinline__ void pm_tile(const ScanParams& p, uint64_t first, uin
   with_form(fam, [&](const auto& f) {
     using F = std::decay_t<decltype(f)>;
     if (p.fast_counter) {
-      const GenPointMajor gen{philox_lane((uint32_t)gg, p.seed)};
+      using Gen = std::conditional_t<Phased<F>::value, GenPointMajorPhased, GenPointMajor>;
+      const Gen gen = Gen::make((uint32_t)gg, p.seed);
       lane_groups<F, T, N>(f, gen, j0, jfull, ragged, tail, acc);
     } else {
       const GenAny gen{gg, p.seed};

@@ -9,13 +9,15 @@
 
 namespace zmc {
 
-// Waves per SIMD asked of the point-major and batch kernels.  FP32 with
-// 4 <= N <= 8 runs faster at 8 (the compiler then keeps 64 VGPRs and spills a
-// few set-up values); at N <= 3, in FP64, and for N > 8 (where 64 VGPRs
-// would spill the per-point constants of every sample) its own choice is
-// taken.
+// Waves per SIMD asked of the point-major and batch kernels: enough for the
+// issue phases to pair (two waves pair 60 % as often as four), and as many as
+// fit without spilling in the loop.  FP32 at 5 against the compiler's own
+// choice: Gaussian N = 8 0.98 vs 1.05 ms, SIN_SUM N = 12 1.31 vs 1.47 ms
+// (5e5 points x 1024 samples); at 6 the N = 12 Gaussian spills (2.03 vs
+// 1.45 ms).  FP64 at 4 up to N = 8 (Gaussian N = 8 1.48 vs 1.63 ms) and 3
+// beyond (Gaussian N = 12 2.07 vs 2.30 ms); at 5 it spills from N = 7.
 template <typename T, int N>
-constexpr int kMinWaves = (sizeof(T) == 4 && N >= 4 && N <= kAnyMaxDims) ? 8 : 1;
+constexpr int kMinWaves = sizeof(T) == 4 ? 5 : N <= kAnyMaxDims ? 4 : 3;
 
 template <class Fam, typename T, int N>
 __global__ __launch_bounds__(256, (kMinWaves<T, N>)) void k_point_major(ScanParams p) {
@@ -83,9 +85,11 @@ __device__ __forceinline__ void run_tile_any(const ScanParams& p, const Tile& tl
 }
 
 // Batched scans, one kernel for every family (N <= kAnyMaxDims) of one
-// working precision: the blocks pop tiles of all scans from one queue.
+// working precision: the blocks pop tiles of all scans from one queue.  FP32
+// fits four waves per SIMD; FP64 spills beyond two (at four waves a served
+// FP64 mix took 3.8 ms instead of 3.1).
 template <typename T>
-__global__ __launch_bounds__(256) void k_batch_any(const ScanParams* __restrict__ scans,
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_batch_any(const ScanParams* __restrict__ scans,
                                                    const Tile* __restrict__ tiles, uint32_t begin,
                                                    uint32_t end, uint32_t* counter) {
   __shared__ uint32_t next;

@@ -18,6 +18,7 @@ namespace zmc {
 template <typename T, int N, int M>
 struct UserFamily {
   static constexpr int kMinDims = 1;
+  static constexpr bool kPhased = sizeof(T) == 8;
   T A[N], B[N];
   T x[M > 0 ? M : 1];
   T q[kMaxUserParams];
