@@ -30,7 +30,7 @@ ARCH = "gfx950"
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 # device headers that the run-time compiler of user integrands needs, embedded
 # into the library as text
-RTC_HEADERS = ("zmc_device.hpp", "zmc_scan.hpp", "zmc_user.hpp")
+RTC_HEADERS = ("zmc_exp2_table.hpp", "zmc_device.hpp", "zmc_scan.hpp", "zmc_user.hpp")
 
 
 def hipcc():

@@ -21,6 +21,8 @@ using __hip_internal::uint64_t;
 
 #include <type_traits>
 
+#include "zmc_exp2_table.hpp"
+
 namespace zmc {
 
 constexpr int kMaxParams = 16;
@@ -385,6 +387,7 @@ constexpr double kLog2e = 1.4426950408889634074;
 // (for |r| >= 2^23 an FP32 phase no longer resolves a revolution and the
 // reduced phase is 0).
 constexpr double kInv2Pi = 0.15915494309189533577;
+constexpr double kInv2PiLo = -9.839338337591243e-18;  // 1/(2 pi) - kInv2Pi
 
 __device__ __forceinline__ float sin_turns(float r) {
   return __builtin_amdgcn_sinf(r - __builtin_rintf(r));
@@ -419,34 +422,79 @@ __host__ __device__ __forceinline__ double sin_2pi_quarter(double v) {
   return v * p;
 }
 
-// FP64 2^t.  k = rint(t) and f = t - k in [-1/2, 1/2] (exact); 2^f by a
-// degree-11 polynomial from Chebyshev economization of the Taylor series of
-// e^(f ln 2) on [-1/2, 1/2] (fp64_poly.py: dropped terms below 3.2e-18,
-// Horner within 1.2e-16 relative); 2^k applied by ldexp.  t is first clamped
-// to [-2100, 2100], beyond which 2^t is 0 or inf in double: -inf then gives
-// 0 and +inf gives inf, as exp does, and k always fits an int (a NaN t is
-// clamped too and gives 0; the parameter values it would come from must be
-// finite).  kNonPositive: the caller guarantees t <= 0 (or NaN), so only the
-// lower clamp is needed.
+// FP64 2^t.  n = rint(256 t) and f = 256 t - n in [-1/2, 1/2] (exact); with
+// j = n mod 256, 2^t = 2^(n div 256) 2^(j/256) 2^(f/256).  2^(j/256) comes from
+// a table in LDS as T (1 + eps), T rounded to double; 2^(f/256) - 1 is a
+// degree-4 polynomial from Chebyshev economization (fp64_poly.py: dropped terms
+// below 2.4e-18); T + T (f P(f) + eps) then carries one rounding (1.113e-16
+// relative at most), and ldexp applies 2^(n div 256).  n is read from the low
+// word of 256 t + 1.5 2^52, whose addition rounds to an integer.
+// FP64 instructions never pair with anything (see the issue phases), so what
+// counts is their number: 11, with three shifts and masks that pair, against 16
+// for a polynomial on [-1/2, 1/2] without a table; the LDS reads (16 bytes a
+// lane, their bank conflicts included) run beside them.  Table size: 64
+// entries need one more fma, 512 save none.
+// t is first clamped to [-2100, 2100], beyond which 2^t is 0 or inf in double:
+// -inf then gives 0 and +inf gives inf, as exp does, and n always fits 32 bits
+// (a NaN t is clamped too and gives 0; the parameter values it would come from
+// must be finite).
+constexpr int kExp2Entries = 256;
+constexpr double kExp2Scale = 256.0;
+constexpr double kRoundMagic = 0x1.8p52;  // x + kRoundMagic: rint(x) in the low word
+
+#if defined(__HIP_DEVICE_COMPILE__)
+static __device__ const double kExp2Table[2 * kExp2Entries] = {ZMC_EXP2_TABLE};
+
+// The block's copy of the table (LDS); exp2_table_load fills it, and every
+// thread of the block must call that before the first 2^t.
+__device__ __forceinline__ double* exp2_table() {
+  __shared__ __align__(16) double table[2 * kExp2Entries];
+  return table;
+}
+
+__device__ __forceinline__ void exp2_table_load() {
+  double* t = exp2_table();
+  for (unsigned i = threadIdx.x; i < 2 * kExp2Entries; i += blockDim.x) t[i] = kExp2Table[i];
+  __syncthreads();
+}
+#else
+inline const double* exp2_table() {
+  static const double table[2 * kExp2Entries] = {ZMC_EXP2_TABLE};
+  return table;
+}
+__host__ __device__ inline void exp2_table_load() {}
+#endif
+
+// 2^(c x) for c x already known to lie in [-2100, 2100]; cs = 256 c.
+__host__ __device__ __forceinline__ double exp2_scaled(double x, double cs) {
+  const double m = __builtin_fma(x, cs, kRoundMagic);
+  const double f = __builtin_fma(x, cs, -(m - kRoundMagic));
+  const int n = (int)(uint32_t)__builtin_bit_cast(uint64_t, m);
+  const double* e = exp2_table() + 2 * (n & (kExp2Entries - 1));
+  const double T = e[0], eps = e[1];
+  double p = 2.239395396091414e-12;
+  p = __builtin_fma(p, f, 3.3083030595039036e-09);
+  p = __builtin_fma(p, f, 3.6655655969100867e-06);
+  p = __builtin_fma(p, f, 0.002707606174062263);
+  p = __builtin_fma(p, f, eps);
+  return __builtin_ldexp(__builtin_fma(T, p, T), n >> 8);
+}
+
+// 2^t.  kNonPositive: the caller guarantees t <= 0 (or NaN), so only the lower
+// clamp is needed.
 template <bool kNonPositive = false>
 __host__ __device__ __forceinline__ double exp2_fp64(double t) {
   t = __builtin_fmax(t, -2100.0);
   if constexpr (!kNonPositive) t = __builtin_fmin(t, 2100.0);
-  const double k = __builtin_rint(t);
-  const double f = t - k;
-  double p = 4.456675463639861e-10;
-  p = __builtin_fma(p, f, 7.074194562613105e-09);
-  p = __builtin_fma(p, f, 1.0178051192117847e-07);
-  p = __builtin_fma(p, f, 1.3215432534254118e-06);
-  p = __builtin_fma(p, f, 1.5252733856295574e-05);
-  p = __builtin_fma(p, f, 0.00015403530463727982);
-  p = __builtin_fma(p, f, 0.001333355814639035);
-  p = __builtin_fma(p, f, 0.009618129107587253);
-  p = __builtin_fma(p, f, 0.0555041086648217);
-  p = __builtin_fma(p, f, 0.24022650695910158);
-  p = __builtin_fma(p, f, 0.6931471805599453);
-  p = __builtin_fma(p, f, 1.0);
-  return __builtin_ldexp(p, (int)k);
+  return exp2_scaled(t, kExp2Scale);
+}
+
+// e^(-q) = 2^(-q log2 e).  kNonNegative: q >= 0 (or NaN, which gives 0).
+template <bool kNonNegative = false>
+__host__ __device__ __forceinline__ double exp_minus_fp64(double q) {
+  q = __builtin_fmin(q, 2100.0 / kLog2e);
+  if constexpr (!kNonNegative) q = __builtin_fmax(q, -2100.0 / kLog2e);
+  return exp2_scaled(q, -kExp2Scale * kLog2e);
 }
 
 __host__ __device__ __forceinline__ double sin_turns(double r) {
@@ -457,6 +505,25 @@ __host__ __device__ __forceinline__ double sin_turns(double r) {
 __host__ __device__ __forceinline__ double cos_turns(double r) {
   const double t = r - __builtin_rint(r);
   return sin_2pi_quarter(0.25 - __builtin_fabs(t));
+}
+
+// Radians to a fraction of a revolution in [-1/2, 1/2], without the rounding of
+// the whole revolutions: |error| below 2^-54 plus 2^-106 |s|.
+__host__ __device__ __forceinline__ double turns_fraction(double s) {
+  const double r = s * kInv2Pi;
+  const double e = __builtin_fma(s, kInv2Pi, -r) + s * kInv2PiLo;
+  return (r - __builtin_rint(r)) + e;
+}
+
+// Families whose FP64 form takes 2^t from the block's table: the kernels load
+// it first.
+template <class Fam, class = void> struct UsesExp2Table : std::false_type {};
+template <class Fam>
+struct UsesExp2Table<Fam, std::void_t<decltype(Fam::kExp2Table)>>
+    : std::integral_constant<bool, Fam::kExp2Table> {};
+
+template <class Fam> __device__ __forceinline__ void load_tables() {
+  if constexpr (UsesExp2Table<Fam>::value) exp2_table_load();
 }
 
 // Parameter x_l of grid point g (C order: stride_l = prod_{j>l} L_j).
@@ -472,10 +539,15 @@ __device__ __forceinline__ double param_x(const ScanParams& p, uint64_t g, int l
 // ---------------------------------------------------------------------------
 
 // sin(sum_l x_l + sum_k y_k): the paper's test integrand, Eq. (2) and Eq. (4).
+// FP64: the phase is summed in radians, coordinate by coordinate as the formula
+// states it (folding the box offsets into the point's constant would save N - 1
+// additions a sample, but moves the phase's roundings by up to 3e-15), and one
+// fma takes it to revolutions less the quarter turn of sin a = cos(a - pi/2),
+// whose reduction needs no compare and select.
 template <typename T, int N> struct SinSum {
   static constexpr int kMinDims = 1;
   T A[N], B[N];
-  T sx;        // FP64: sum of x; FP32: sum x + sum B (all in revolutions)
+  T sx;        // FP64: sum of x; FP32: sum x + sum B (A and sx in revolutions)
   __device__ void setup(const ScanParams& p, uint64_t g) {
     double s = 0.0, sb = 0.0;
     for (int l = 0; l < p.M; ++l) s += param_x(p, g, l);
@@ -483,18 +555,18 @@ template <typename T, int N> struct SinSum {
     for (int k = 0; k < N; ++k) {
       double a, b;
       Unif<T>::affine(p.lo[k], p.hi[k], &a, &b);
-      A[k] = (T)(a * kInv2Pi);
-      B[k] = (T)(b * kInv2Pi);
+      A[k] = sizeof(T) == 8 ? (T)a : (T)(a * kInv2Pi);
+      B[k] = (T)b;
       sb += b;
     }
-    sx = sizeof(T) == 8 ? (T)(s * kInv2Pi) : (T)((s + sb) * kInv2Pi);
+    sx = sizeof(T) == 8 ? (T)s : (T)((s + sb) * kInv2Pi);
   }
   __device__ __forceinline__ T value(const T* t) const {
     if constexpr (sizeof(T) == 8) {
-      double sy = 0.0;
+      double sy = fmaT(A[0], t[0], B[0]);
 #pragma unroll
-      for (int k = 0; k < N; ++k) sy += fmaT(A[k], t[k], B[k]);
-      return sin_turns(sx + sy);
+      for (int k = 1; k < N; ++k) sy += fmaT(A[k], t[k], B[k]);
+      return cos_turns(__builtin_fma(sx + sy, kInv2Pi, -0.25));
     } else {
       float ph = sx;
 #pragma unroll
@@ -523,7 +595,7 @@ template <typename T, int N> struct GaussUnit {
       q = k == 0 ? z * z : fmaT(z, z, q);
     }
     if constexpr (sizeof(T) == 8) {
-      return exp2_fp64<true>(q * -kLog2e);  // q, a sum of squares, is >= 0
+      return exp_minus_fp64<true>(q);  // q, a sum of squares, is >= 0
     } else {
       return __builtin_amdgcn_exp2f(-q);
     }
@@ -532,6 +604,7 @@ template <typename T, int N> struct GaussUnit {
 
 template <typename T, int N> struct Gauss {
   static constexpr int kMinDims = 1;
+  static constexpr bool kExp2Table = sizeof(T) == 8;
   using UnitForm = GaussUnit<T, N>;
   T A[N], B[N], c[N];   // FP32: c carries log2(e) for exp2
   bool unit;            // wave-uniform: c_k = 1 on every active lane of the wave
@@ -572,7 +645,7 @@ template <typename T, int N> struct Gauss {
       q = k == 0 ? (c[k] * y) * y : fmaT(c[k] * y, y, q);
     }
     if constexpr (sizeof(T) == 8) {
-      return exp2_fp64(q * -kLog2e);
+      return exp_minus_fp64(q);
     } else {
       return __builtin_amdgcn_exp2f(-q);
     }
@@ -580,11 +653,13 @@ template <typename T, int N> struct Gauss {
 };
 
 // cos(x1 y1 + x2 y2 + sum_{k>=3} y_k) exp(-x3^2 y1 y2) + x4.
-template <typename T, int N> struct CosExp {
+template <typename T, int N> struct CosExp;
+
+template <int N> struct CosExp<float, N> {
   static constexpr int kMinDims = 2;
-  T A[N], B[N];
-  T x1, x2, nx3sq, x4;  // nx3sq = -x3^2 log2(e): the exponential is evaluated as 2^t
-  T rest;               // FP32: sum of B_k for k >= 3, folded into the phase
+  float A[N], B[N];
+  float x1, x2, nx3sq, x4;  // nx3sq = -x3^2 log2(e): the exponential is evaluated as 2^t
+  float rest;               // sum of B_k for k >= 3, folded into the phase
   // x1, x2, rest and A_k, B_k (k >= 3) in revolutions (times 1/(2 pi))
   __device__ void setup(const ScanParams& p, uint64_t g) {
     const double turn = kInv2Pi;
@@ -592,39 +667,72 @@ template <typename T, int N> struct CosExp {
 #pragma unroll
     for (int k = 0; k < N; ++k) {
       double a, b;
-      Unif<T>::affine(p.lo[k], p.hi[k], &a, &b);
-      A[k] = (T)(k >= 2 ? a * turn : a);
-      B[k] = (T)(k >= 2 && sizeof(T) == 8 ? b * turn : b);
+      Unif<float>::affine(p.lo[k], p.hi[k], &a, &b);
+      A[k] = (float)(k >= 2 ? a * turn : a);
+      B[k] = (float)b;
       if (k >= 2) sb += b;
     }
-    x1 = (T)(param_x(p, g, 0) * turn);
-    x2 = (T)(param_x(p, g, 1) * turn);
+    x1 = (float)(param_x(p, g, 0) * turn);
+    x2 = (float)(param_x(p, g, 1) * turn);
     const double x3 = param_x(p, g, 2);
-    nx3sq = (T)(-(x3 * x3) * kLog2e);
-    x4 = (T)param_x(p, g, 3);
-    rest = (T)(sb * turn);
+    nx3sq = (float)(-(x3 * x3) * kLog2e);
+    x4 = (float)param_x(p, g, 3);
+    rest = (float)(sb * turn);
   }
-  __device__ __forceinline__ T value(const T* t) const {
-    const T y1 = fmaT(A[0], t[0], B[0]);
-    const T y2 = fmaT(A[1], t[1], B[1]);
-    if constexpr (sizeof(T) == 8) {
-      double ph = x1 * y1 + x2 * y2;
-#pragma unroll
-      for (int k = 2; k < N; ++k) ph += fmaT(A[k], t[k], B[k]);
-      return __builtin_fma(cos_turns(ph), exp2_fp64(nx3sq * y1 * y2), x4);
+  __device__ __forceinline__ float value(const float* t) const {
+    const float y1 = fmaT(A[0], t[0], B[0]);
+    const float y2 = fmaT(A[1], t[1], B[1]);
+    float ph;
+    if constexpr (N == 2) {
+      ph = fmaT(x1, y1, x2 * y2);  // no further terms: no zero addend
     } else {
-      float ph;
-      if constexpr (N == 2) {
-        ph = fmaT(x1, y1, x2 * y2);  // no further terms: no zero addend
-      } else {
-        ph = rest;
+      ph = rest;
 #pragma unroll
-        for (int k = 2; k < N; ++k) ph = fmaT(A[k], t[k], ph);
-        ph = fmaT(x1, y1, fmaT(x2, y2, ph));
-      }
-      const float e = __builtin_amdgcn_exp2f(nx3sq * y1 * y2);
-      return fmaT(cos_turns(ph), e, x4);
+      for (int k = 2; k < N; ++k) ph = fmaT(A[k], t[k], ph);
+      ph = fmaT(x1, y1, fmaT(x2, y2, ph));
     }
+    const float e = __builtin_amdgcn_exp2f(nx3sq * y1 * y2);
+    return fmaT(cos_turns(ph), e, x4);
+  }
+};
+
+// FP64: the phase and the exponent's first factor are linear in the variates,
+// so the point's parameters are folded into their coefficients at set-up:
+//   phase / (2 pi) = C + P1 t1 + P2 t2 + sum_{k>=3} A_k t_k  (C modulo 1)
+//   exponent = (E t1 + F) y2, y2 = A2 t2 + B2
+// i.e. N + 3 instructions instead of 2 N + 2 and the additions.
+template <int N> struct CosExp<double, N> {
+  static constexpr int kMinDims = 2;
+  static constexpr bool kExp2Table = true;
+  double P[N];        // P1, P2, then A_k, in revolutions
+  double C, E, F, A2, B2, x4;
+  __device__ void setup(const ScanParams& p, uint64_t g) {
+    double a[N], b[N], sb = 0.0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      Unif<double>::affine(p.lo[k], p.hi[k], &a[k], &b[k]);
+      if (k >= 2) {
+        P[k] = a[k] * kInv2Pi;
+        sb += b[k];
+      }
+    }
+    const double x1 = param_x(p, g, 0), x2 = param_x(p, g, 1), x3 = param_x(p, g, 2);
+    P[0] = x1 * kInv2Pi * a[0];
+    P[1] = x2 * kInv2Pi * a[1];
+    C = turns_fraction(x1 * b[0]) + turns_fraction(x2 * b[1]) + turns_fraction(sb);
+    const double nx3sq = -(x3 * x3) * kLog2e;  // the exponential is evaluated as 2^t
+    E = nx3sq * a[0];
+    F = nx3sq * b[0];
+    A2 = a[1];
+    B2 = b[1];
+    x4 = param_x(p, g, 3);
+  }
+  __device__ __forceinline__ double value(const double* t) const {
+    double ph = C;
+#pragma unroll
+    for (int k = 0; k < N; ++k) ph = fmaT(P[k], t[k], ph);
+    const double e = fmaT(E, t[0], F) * fmaT(A2, t[1], B2);
+    return __builtin_fma(cos_turns(ph), exp2_fp64(e), x4);
   }
 };
 

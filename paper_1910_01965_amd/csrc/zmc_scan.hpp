@@ -161,12 +161,14 @@ __device__ __forceinline__ void merge_point(const ScanParams& p, uint64_t g) {
 // (debugging, parity).
 template <class Fam, typename T, int N>
 __device__ __forceinline__ void point_major_body(const ScanParams& p) {
+  load_tables<Fam>();
   for (uint64_t pb = blockIdx.x; pb < p.point_blocks; pb += gridDim.x)
     pm_tile<Fam, T, N>(p, pb * blockDim.x, blockIdx.y);
 }
 
 template <class Fam, typename T, int N>
 __device__ __forceinline__ void sample_major_body(const ScanParams& p, double* lds) {
+  load_tables<Fam>();
   for (uint64_t g = blockIdx.x; g < p.G; g += gridDim.x) sm_tile<Fam, T, N>(p, g, blockIdx.y, lds);
 }
 
@@ -179,6 +181,7 @@ __device__ __forceinline__ void batch_body(const ScanParams* __restrict__ scans,
                                            const Tile* __restrict__ tiles, uint32_t begin,
                                            uint32_t end, uint32_t* counter, uint32_t* next,
                                            double* lds) {
+  load_tables<Fam>();
   for (;;) {
     __syncthreads();  // the previous tile is done with `next` and `lds`
     if (threadIdx.x == 0) *next = begin + atomicAdd(counter, 1u);
@@ -199,6 +202,7 @@ __device__ __forceinline__ void batch_body(const ScanParams* __restrict__ scans,
 template <class Fam, typename T, int N>
 __device__ __forceinline__ void debug_values_body(const ScanParams& p, uint64_t g, uint64_t s0,
                                                   int64_t count, double* out) {
+  load_tables<Fam>();
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
   const uint64_t s = s0 + (uint64_t)i;

@@ -94,6 +94,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_batch_any(const
                                                    uint32_t end, uint32_t* counter) {
   __shared__ uint32_t next;
   __shared__ double lds[48];
+  if constexpr (sizeof(T) == 8) exp2_table_load();
   for (;;) {
     __syncthreads();
     if (threadIdx.x == 0) next = begin + atomicAdd(counter, 1u);

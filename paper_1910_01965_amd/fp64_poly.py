@@ -6,7 +6,9 @@ digits), rewritten in the Chebyshev basis of the interval, cut after the
 stated degree (the dropped Chebyshev coefficients bound the truncation
 error), rewritten in powers of the argument and rounded to double.
 
-  exp2:  2^f = sum_{n=0..11} e_n f^n          for f in [-1/2, 1/2]
+  exp2:  2^(f/256) = 1 + sum_{n=1..4} e_n f^n     for f in [-1/2, 1/2], and the
+         table of 2^(j/256), j = 0..255, as a rounded value and its relative
+         remainder (csrc/zmc_exp2_table.hpp, written by --table)
   sin:   sin(2 pi v) = v sum_{k=0..8} s_k v^(2k)  for v in [-1/4, 1/4]
 
 Run `python -m paper_1910_01965_amd.fp64_poly` to print the constants and
@@ -14,6 +16,8 @@ the largest relative error of the double-precision Horner evaluation on a
 dense grid against a 60-digit reference.
 """
 import math
+import os
+import sys
 from decimal import Decimal, getcontext
 from fractions import Fraction as Fr
 
@@ -54,11 +58,34 @@ def _economize(a, d):
     return p, dropped
 
 
-def exp2_coefficients(degree=11):
-    """e_0..e_degree of 2^f on [-1/2, 1/2] (f = x / 2)."""
-    a = [(LN2 / 2) ** n / math.factorial(n) for n in range(DEGREE_TAYLOR + 1)]
+EXP2_ENTRIES = 256
+
+
+def exp2_coefficients(degree=4):
+    """e_1..e_degree of (2^(f/256) - 1) on [-1/2, 1/2] (f = x / 2)."""
+    a = [Fr(0)] + [(LN2 / (2 * EXP2_ENTRIES)) ** n / math.factorial(n)
+                   for n in range(1, DEGREE_TAYLOR + 1)]
     p, dropped = _economize(a, degree)
-    return [float(pn * 2 ** n) for n, pn in enumerate(p)], float(dropped)
+    return [float(p[n] * 2 ** n) for n in range(1, degree + 1)], float(dropped + abs(p[0]))
+
+
+def exp2_table():
+    """(T, eps): 2^(j/256) = T (1 + eps), T rounded to double."""
+    out = []
+    for j in range(EXP2_ENTRIES):
+        exact = Decimal(2) ** (Decimal(j) / EXP2_ENTRIES)
+        t = float(exact)
+        out.append((t, float(exact / Decimal(t) - 1)))
+    return out
+
+
+def write_table():
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "zmc_exp2_table.hpp")
+    rows = ["  {}, {},  \\".format(t.hex(), e.hex()) for t, e in exp2_table()]
+    with open(path, "w") as fh:
+        fh.write("// zmc_exp2_table.hpp -- 2^(j/256), j = 0..255, as pairs (T, eps): 2^(j/256) =\n"
+                 "// T (1 + eps) with T rounded to double.  Written by fp64_poly.py --table.\n"
+                 "#pragma once\n\n#define ZMC_EXP2_TABLE  \\\n" + "\n".join(rows)[:-4] + "\n")
 
 
 def sin_coefficients(degree=17):
@@ -86,9 +113,10 @@ def _horner(coef, x):
 def main():
     e, de = exp2_coefficients()
     s, ds = sin_coefficients()
-    print(f"// exp2: degree {len(e) - 1}, dropped Chebyshev terms {de:.2e}")
+    print(f"// exp2: degree {len(e)}, dropped Chebyshev terms {de:.2e}")
     for n, c in enumerate(e):
-        print(f"  e{n} = {c!r}")
+        print(f"  e{n + 1} = {c!r}")
+    table = exp2_table()
     print(f"// sin(2 pi v) / v: {len(s)} terms, dropped Chebyshev terms {ds:.2e}")
     for k, c in enumerate(s):
         print(f"  s{k} = {c!r}")
@@ -96,8 +124,9 @@ def main():
     pi = Decimal(PI.numerator) / Decimal(PI.denominator)
     for i in range(-4000, 4001):
         f = i / 8000.0
-        ref = Decimal(2) ** Decimal(f)
-        got = _horner(e, f)
+        t, eps = table[i % EXP2_ENTRIES]
+        ref = Decimal(2) ** ((Decimal(i % EXP2_ENTRIES) + Decimal(f)) / EXP2_ENTRIES)
+        got = _fma(t, _fma(f, _horner(e, f), eps), t)
         worst_e = max(worst_e, abs((Decimal(got) - ref) / ref))
         v = i / 16000.0
         if v != 0.0:
@@ -118,4 +147,6 @@ def _dsin(x):
 
 
 if __name__ == "__main__":
+    if "--table" in sys.argv:
+        write_table()
     main()
