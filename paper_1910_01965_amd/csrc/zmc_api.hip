@@ -218,6 +218,11 @@ zmc_status make_plan(const zmc_scan_desc* d, uint64_t G, const zmc_launch_opts* 
     if (splits < 1) splits = 1;
     while (splits > 1 && 16.0 * (double)splits * (double)G > (double)kMaxWorkspace) splits /= 2;
   }
+  // a sample-major piece that gives no lane a second group leaves the lanes past
+  // it idle: only the waves that have work are launched (the same lanes take the
+  // same groups)
+  if (mode == ZMC_MODE_SAMPLE_MAJOR && !(o && o->block > 0) && splits <= 1 && groups < (uint64_t)block)
+    block = (int)(cdiv(groups, 64) * 64);
   if (splits > (uint64_t)kMaxSplits) splits = kMaxSplits;
   if (splits > groups) splits = groups;
   const uint64_t gps = cdiv(groups, splits);

@@ -253,6 +253,48 @@ __host__ __device__ __forceinline__ Words4 philox_block_pm(uint32_t b, const Phi
   return w;
 }
 
+// Rounds 4..10 of NB blocks in phases: words 0 and 2 in c0, c2, words 1 and 3 in
+// the low halves of round 3's products q, p; kv as in_vgpr keys.
+template <int NB>
+__host__ __device__ __forceinline__ void philox_key_rounds(uint32_t (&c0)[NB], uint32_t (&c2)[NB],
+                                                           uint64_t (&p)[NB], uint64_t (&q)[NB],
+                                                           const uint32_t* kv, Words4 w[NB]) {
+#pragma unroll
+  for (int r = 0; r < kKeyRounds; ++r) {
+    uint64_t pp[NB], qq[NB];
+    phase_mul<NB>(c0, c2);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      pp[i] = (uint64_t)kPhiloxM0 * c0[i];
+      qq[i] = (uint64_t)kPhiloxM1 * c2[i];
+    }
+    phase_int<NB>(pp, qq);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      c0[i] = xor3((uint32_t)(qq[i] >> 32), (uint32_t)q[i], kv[2 * r]);
+      c2[i] = xor3((uint32_t)(pp[i] >> 32), (uint32_t)p[i], kv[2 * r + 1]);
+      p[i] = pp[i];
+      q[i] = qq[i];
+    }
+  }
+  phase_float<NB>(c0, c2);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    w[i].r[0] = c0[i];
+    w[i].r[1] = (uint32_t)q[i];
+    w[i].r[2] = c2[i];
+    w[i].r[3] = (uint32_t)p[i];
+  }
+}
+
+__host__ __device__ __forceinline__ void philox_vgpr_keys(uint64_t seed, uint32_t* kv) {
+#pragma unroll
+  for (int i = 0; i < kKeyRounds; ++i) {
+    kv[2 * i] = in_vgpr((uint32_t)seed + (uint32_t)(3 + i) * kPhiloxW0);
+    kv[2 * i + 1] = in_vgpr((uint32_t)(seed >> 32) + (uint32_t)(3 + i) * kPhiloxW1);
+  }
+}
+
 // The same with what the issue phases need.
 struct PhiloxPhasedLane {
   PhiloxLane L;
@@ -264,11 +306,7 @@ __host__ __device__ __forceinline__ PhiloxPhasedLane philox_phased_lane(uint32_t
   PhiloxPhasedLane P;
   P.L = philox_lane(g, seed);
   P.l2k = P.L.l2 ^ (P.L.k1 + 2 * kPhiloxW1);
-#pragma unroll
-  for (int i = 0; i < kKeyRounds; ++i) {
-    P.kv[2 * i] = in_vgpr(P.L.k0 + (uint32_t)(3 + i) * kPhiloxW0);
-    P.kv[2 * i + 1] = in_vgpr(P.L.k1 + (uint32_t)(3 + i) * kPhiloxW1);
-  }
+  philox_vgpr_keys(seed, P.kv);
   return P;
 }
 
@@ -292,7 +330,7 @@ __host__ __device__ __forceinline__ void philox_blocks_pm(uint32_t b0, const Phi
     c2[i] = L.h2 ^ (u3 ^ k1b);
     u1[i] = (uint32_t)q1 ^ (L.k0 + 2 * kPhiloxW0);
   }
-  uint64_t p[NB], q[NB], pp[NB], qq[NB];
+  uint64_t p[NB], q[NB];
   phase_mul<NB>(c0, c2);
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
@@ -307,31 +345,67 @@ __host__ __device__ __forceinline__ void philox_blocks_pm(uint32_t b0, const Phi
     c0[i] = (uint32_t)(q[i] >> 32) ^ u1[i];
     c2[i] = (uint32_t)(p[i] >> 32) ^ P.l2k;
   }
-#pragma unroll
-  for (int r = 0; r < kKeyRounds; ++r) {
-    phase_mul<NB>(c0, c2);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      pp[i] = (uint64_t)kPhiloxM0 * c0[i];
-      qq[i] = (uint64_t)kPhiloxM1 * c2[i];
-    }
-    phase_int<NB>(pp, qq);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      c0[i] = xor3((uint32_t)(qq[i] >> 32), (uint32_t)q[i], P.kv[2 * r]);
-      c2[i] = xor3((uint32_t)(pp[i] >> 32), (uint32_t)p[i], P.kv[2 * r + 1]);
-      p[i] = pp[i];
-      q[i] = qq[i];
-    }
-  }
-  phase_float<NB>(c0, c2);
+  philox_key_rounds<NB>(c0, c2, p, q, P.kv, w);
+}
+
+// ---------------------------------------------------------------------------
+// The sample-major mirror (b < 2^32, g < 2^32): the wave shares g and its lanes
+// differ in b, so round 1's M1 g and round 2's M0 product are wave-uniform.
+// 18 products per lane and block instead of 20, and the xors in phases.  Uniform
+// values sit in vector registers (see the issue phases).
+// ---------------------------------------------------------------------------
+struct PhiloxPoint {
+  uint32_t k1;                  // the second key of round 1
+  uint32_t u1;                  // round-1 word 1 ^ round 2's first key
+  uint32_t x0;                  // hi(M0 * round-1 word 0) ^ round 2's second key
+  uint32_t x3;                  // lo(M0 * round-1 word 0) ^ round 3's second key
+  uint32_t k03;                 // round 3's first key
+  uint32_t kv[2 * kKeyRounds];  // keys of rounds 4..10
+};
+
+__host__ __device__ __forceinline__ PhiloxPoint philox_point(uint32_t g, uint64_t seed) {
+  const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+  const uint64_t p1 = (uint64_t)kPhiloxM1 * g;
+  const uint64_t p2 = (uint64_t)kPhiloxM0 * ((uint32_t)(p1 >> 32) ^ k0);  // counter word 1 is 0
+  PhiloxPoint P;
+  P.k1 = in_vgpr(k1);
+  P.u1 = in_vgpr((uint32_t)p1 ^ (k0 + kPhiloxW0));
+  P.x0 = in_vgpr((uint32_t)(p2 >> 32) ^ (k1 + kPhiloxW1));
+  P.x3 = in_vgpr((uint32_t)p2 ^ (k1 + 2 * kPhiloxW1));
+  P.k03 = in_vgpr(k0 + 2 * kPhiloxW0);
+  philox_vgpr_keys(seed, P.kv);
+  return P;
+}
+
+// Blocks b0 .. b0 + NB - 1 (b0 per lane), NB <= kMaxBatch.
+template <int NB>
+__host__ __device__ __forceinline__ void philox_blocks_sm(uint32_t b0, const PhiloxPoint& P, Words4 w[NB]) {
+  uint32_t c0[NB], c2[NB];
+  uint64_t p[NB], q[NB], r2[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    w[i].r[0] = c0[i];
-    w[i].r[1] = (uint32_t)q[i];
-    w[i].r[2] = c2[i];
-    w[i].r[3] = (uint32_t)p[i];
+    p[i] = (uint64_t)kPhiloxM0 * (b0 + (uint32_t)i);               // round 1
+    r2[i] = (uint64_t)kPhiloxM1 * ((uint32_t)(p[i] >> 32) ^ P.k1);  // round 2 (counter word 3 is 0)
   }
+  phase_int<NB>(p, r2);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    c0[i] = (uint32_t)(r2[i] >> 32) ^ P.u1;
+    c2[i] = (uint32_t)p[i] ^ P.x0;
+  }
+  phase_mul<NB>(c0, c2);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    p[i] = (uint64_t)kPhiloxM0 * c0[i];  // round 3
+    q[i] = (uint64_t)kPhiloxM1 * c2[i];
+  }
+  phase_int<NB>(p, q);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    c0[i] = xor3((uint32_t)(q[i] >> 32), (uint32_t)r2[i], P.k03);
+    c2[i] = (uint32_t)(p[i] >> 32) ^ P.x3;
+  }
+  philox_key_rounds<NB>(c0, c2, p, q, P.kv, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -465,10 +539,8 @@ inline const double* exp2_table() {
 __host__ __device__ inline void exp2_table_load() {}
 #endif
 
-// 2^(c x) for c x already known to lie in [-2100, 2100]; cs = 256 c.
-__host__ __device__ __forceinline__ double exp2_scaled(double x, double cs) {
-  const double m = __builtin_fma(x, cs, kRoundMagic);
-  const double f = __builtin_fma(x, cs, -(m - kRoundMagic));
+// 2^(u / 256), u = n + f, m = n + kRoundMagic.
+__host__ __device__ __forceinline__ double exp2_parts(double m, double f) {
   const int n = (int)(uint32_t)__builtin_bit_cast(uint64_t, m);
   const double* e = exp2_table() + 2 * (n & (kExp2Entries - 1));
   const double T = e[0], eps = e[1];
@@ -480,13 +552,20 @@ __host__ __device__ __forceinline__ double exp2_scaled(double x, double cs) {
   return __builtin_ldexp(__builtin_fma(T, p, T), n >> 8);
 }
 
+// 2^(u / 256), for callers that scale the exponent by 256 in their constants.
+__host__ __device__ __forceinline__ double exp2_units(double u) {
+  u = __builtin_fmin(__builtin_fmax(u, -2100.0 * kExp2Scale), 2100.0 * kExp2Scale);
+  const double m = u + kRoundMagic;
+  return exp2_parts(m, u - (m - kRoundMagic));
+}
+
 // 2^t.  kNonPositive: the caller guarantees t <= 0 (or NaN), so only the lower
 // clamp is needed.
 template <bool kNonPositive = false>
 __host__ __device__ __forceinline__ double exp2_fp64(double t) {
   t = __builtin_fmax(t, -2100.0);
   if constexpr (!kNonPositive) t = __builtin_fmin(t, 2100.0);
-  return exp2_scaled(t, kExp2Scale);
+  return exp2_units(t * kExp2Scale);
 }
 
 // e^(-q) = 2^(-q log2 e).  kNonNegative: q >= 0 (or NaN, which gives 0).
@@ -494,7 +573,9 @@ template <bool kNonNegative = false>
 __host__ __device__ __forceinline__ double exp_minus_fp64(double q) {
   q = __builtin_fmin(q, 2100.0 / kLog2e);
   if constexpr (!kNonNegative) q = __builtin_fmax(q, -2100.0 / kLog2e);
-  return exp2_scaled(q, -kExp2Scale * kLog2e);
+  constexpr double cs = -kExp2Scale * kLog2e;
+  const double m = __builtin_fma(q, cs, kRoundMagic);
+  return exp2_parts(m, __builtin_fma(q, cs, -(m - kRoundMagic)));
 }
 
 __host__ __device__ __forceinline__ double sin_turns(double r) {
@@ -720,7 +801,7 @@ template <int N> struct CosExp<double, N> {
     P[0] = x1 * kInv2Pi * a[0];
     P[1] = x2 * kInv2Pi * a[1];
     C = turns_fraction(x1 * b[0]) + turns_fraction(x2 * b[1]) + turns_fraction(sb);
-    const double nx3sq = -(x3 * x3) * kLog2e;  // the exponential is evaluated as 2^t
+    const double nx3sq = -(x3 * x3) * kLog2e * kExp2Scale;  // the exponential as 2^(u / 256)
     E = nx3sq * a[0];
     F = nx3sq * b[0];
     A2 = a[1];
@@ -732,7 +813,7 @@ template <int N> struct CosExp<double, N> {
 #pragma unroll
     for (int k = 0; k < N; ++k) ph = fmaT(P[k], t[k], ph);
     const double e = fmaT(E, t[0], F) * fmaT(A2, t[1], B2);
-    return __builtin_fma(cos_turns(ph), exp2_fp64(e), x4);
+    return __builtin_fma(cos_turns(ph), exp2_units(e), x4);
   }
 };
 
@@ -805,6 +886,19 @@ struct GenPointMajorPhased {
   template <typename T> __device__ __forceinline__ GenPointMajorPhased after(T& v) const {
     GenPointMajorPhased g = *this;
     asm("" : "+v"(g.P.L.r1), "+v"(v));
+    return g;
+  }
+};
+
+struct GenSampleMajorPhased {
+  PhiloxPoint P;
+  template <int NB>
+  __device__ __forceinline__ void blocks(uint64_t b, Words4 w[NB]) const {
+    philox_blocks_sm<NB>((uint32_t)b, P, w);
+  }
+  template <typename T> __device__ __forceinline__ GenSampleMajorPhased after(T& v) const {
+    GenSampleMajorPhased g = *this;
+    asm("" : "+v"(g.P.k1), "+v"(v));
     return g;
   }
 };
@@ -970,19 +1064,23 @@ __device__ __forceinline__ Moments merge(const Moments& a, const Moments& b) {
   return m;
 }
 
-// Butterfly over the 64 lanes; every lane ends with the merge of all 64,
-// combined in lane order at every level.
-__device__ __forceinline__ Moments wave_merge(Moments m) {
-  const int lane = (int)(threadIdx.x & 63u);
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    Moments o;
-    o.n = __shfl_xor(m.n, off, 64);
-    o.mean = __shfl_xor(m.mean, off, 64);
-    o.m2 = __shfl_xor(m.m2, off, 64);
-    m = (lane & off) ? merge(o, m) : merge(m, o);
-  }
-  return m;
+// Sum over the 64 lanes in a fixed tree; every lane gets it.  Levels 1 to 8 move
+// the value by DPP within rows of 16 lanes, 16 and 32 by a shuffle.
+template <int Ctrl> __device__ __forceinline__ double dpp_move(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, Ctrl, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), Ctrl, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+__device__ __forceinline__ double wave_sum(double x) {
+  x += dpp_move<0xB1>(x);   // quad_perm [1,0,3,2]
+  x += dpp_move<0x4E>(x);   // quad_perm [2,3,0,1]
+  x += dpp_move<0x141>(x);  // row_half_mirror: the other quad of eight lanes
+  x += dpp_move<0x140>(x);  // row_mirror: the other half of sixteen
+  x += __shfl_xor(x, 16, 64);
+  x += __shfl_xor(x, 32, 64);
+  return x;
 }
 
 // Samples in split sp (groups [sp*gps, min((sp+1)*gps, n_groups)), the last

@@ -76,7 +76,7 @@ hipError_t launch_rate_probe(int32_t op, int32_t blocks, int64_t iters, uint64_t
 
 // Kernels of a user integrand for one (precision, N, M), built on first use.
 struct UserKernels {
-  hipFunction_t pm = nullptr, sm = nullptr, values = nullptr, batch = nullptr;
+  hipFunction_t pm = nullptr, sm = nullptr, sm_big = nullptr, values = nullptr, batch = nullptr;
 };
 zmc_status user_kernels(const zmc_integrand* h, int precision, int N, int M, UserKernels* out);
 hipError_t launch_user_scan(const UserKernels& k, const ScanParams& p, const Plan& plan,

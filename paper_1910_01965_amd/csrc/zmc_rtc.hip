@@ -40,7 +40,7 @@ constexpr size_t kMaxLogInError = 4000;
 
 struct Loaded {
   hipModule_t module = nullptr;
-  hipFunction_t pm = nullptr, sm = nullptr, values = nullptr, batch = nullptr;
+  hipFunction_t pm = nullptr, sm = nullptr, sm_big = nullptr, values = nullptr, batch = nullptr;
 };
 
 std::string program_text(const std::string& user, int precision, int N, int M) {
@@ -54,12 +54,15 @@ std::string program_text(const std::string& user, int precision, int N, int M) {
                           std::to_string(M) + ">, " + T + ", " + std::to_string(N);
   s += "extern \"C\" __global__ __launch_bounds__(256) void zmc_user_point_major(zmc::ScanParams p) {\n";
   s += "  zmc::point_major_body<" + fam + ">(p);\n}\n";
-  // sample-major blocks of N > 8 hold at most 256 threads (the planner's limit),
-  // which leaves each lane up to 256 VGPRs
-  const int sm_threads = N > zmc::kAnyMaxDims ? 256 : 1024;
-  s += "extern \"C\" __global__ __launch_bounds__(" + std::to_string(sm_threads) +
-       ") void zmc_user_sample_major(zmc::ScanParams p) {\n";
-  s += "  __shared__ double lds[48];\n  zmc::sample_major_body<" + fam + ">(p, lds);\n}\n";
+  // sample-major blocks of up to 256 threads (every automatic plan and all of
+  // N > 8), and of up to 1024 for explicit plans, whose bound of 128 VGPRs a lane
+  // can make FP64 integrands spill
+  for (const char* big : {"", "_1024"}) {
+    if (*big && N > zmc::kAnyMaxDims) continue;
+    s += std::string("extern \"C\" __global__ __launch_bounds__(") + (*big ? "1024" : "256") +
+         ") void zmc_user_sample_major" + big + "(zmc::ScanParams p) {\n";
+    s += "  __shared__ double lds[48];\n  zmc::sample_major_body<" + fam + ">(p, lds);\n}\n";
+  }
   s += "extern \"C\" __global__ __launch_bounds__(256) void zmc_user_values(zmc::ScanParams p, "
        "uint64_t g, uint64_t s0, int64_t count, double* out) {\n";
   s += "  zmc::debug_values_body<" + fam + ">(p, g, s0, count, out);\n}\n";
@@ -149,6 +152,8 @@ zmc_status user_kernels(const zmc_integrand* hc, int precision, int N, int M, Us
     e = hipModuleLoadData(&mod, co.data());
     if (e == hipSuccess) e = hipModuleGetFunction(&L.pm, mod, "zmc_user_point_major");
     if (e == hipSuccess) e = hipModuleGetFunction(&L.sm, mod, "zmc_user_sample_major");
+    if (e == hipSuccess && N <= zmc::kAnyMaxDims)
+      e = hipModuleGetFunction(&L.sm_big, mod, "zmc_user_sample_major_1024");
     if (e == hipSuccess) e = hipModuleGetFunction(&L.values, mod, "zmc_user_values");
     if (e == hipSuccess) e = hipModuleGetFunction(&L.batch, mod, "zmc_user_batch");
     if (e != hipSuccess) {
@@ -160,6 +165,7 @@ zmc_status user_kernels(const zmc_integrand* hc, int precision, int N, int M, Us
   }
   out->pm = L.pm;
   out->sm = L.sm;
+  out->sm_big = L.sm_big;
   out->values = L.values;
   out->batch = L.batch;
   return ok();
@@ -182,7 +188,8 @@ hipError_t launch_user_scan(const UserKernels& k, const ScanParams& p, const Pla
   if (ev_begin != nullptr) e = hipEventRecord(ev_begin, stream);
   ScanParams arg = p;
   void* args[] = {&arg};
-  const hipFunction_t f = plan.mode == ZMC_MODE_POINT_MAJOR ? k.pm : k.sm;
+  const hipFunction_t f = plan.mode == ZMC_MODE_POINT_MAJOR ? k.pm : plan.block > 256 ? k.sm_big : k.sm;
+  if (f == nullptr) return hipErrorInvalidValue;  // the planner refuses such blocks
   if (e == hipSuccess)
     e = hipModuleLaunchKernel(f, (unsigned)plan.grid_x, (unsigned)plan.splits, 1, (unsigned)plan.block,
                               1, 1, 0, stream, args, nullptr);

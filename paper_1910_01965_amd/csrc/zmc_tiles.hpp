@@ -24,13 +24,17 @@ __global__ __launch_bounds__(256, (kMinWaves<T, N>)) void k_point_major(ScanPara
   point_major_body<Fam, T, N>(p);
 }
 
-// Threads per sample-major block: up to 1024, or 256 for N > kAnyMaxDims,
-// whose per-point constants and variates need more than the 128 VGPRs that a
-// 1024-thread block leaves each lane.
-template <int N> constexpr int kSmMaxThreads = N > kAnyMaxDims ? 256 : 1024;
+// Sample-major kernels: blocks of up to 256 threads (every automatic plan), or
+// up to 1024 for N <= kAnyMaxDims (explicit plans), whose bound of 128 VGPRs a
+// lane makes the FP64 kernels spill.  One or two waves per SIMD less than for
+// the point-major kernels: the lane's word block and the point's Philox constants
+// take some 20 VGPRs more.
+template <typename T, int N>
+constexpr int kSmMinWaves = sizeof(T) == 4 ? 4 : N <= 5 ? 3 : 2;
 
-template <class Fam, typename T, int N>
-__global__ __launch_bounds__(kSmMaxThreads<N>) void k_sample_major(ScanParams p) {
+template <class Fam, typename T, int N, int MaxThreads>
+__global__ __launch_bounds__(MaxThreads, (MaxThreads > 256 ? 1 : kSmMinWaves<T, N>))
+void k_sample_major(ScanParams p) {
   __shared__ double lds[48];
   sample_major_body<Fam, T, N>(p, lds);
 }
@@ -127,8 +131,12 @@ struct FamilyOps {
     const dim3 grid((unsigned)plan.grid_x, (unsigned)plan.splits);
     if (plan.mode == ZMC_MODE_POINT_MAJOR) {
       hipLaunchKernelGGL((k_point_major<F<T, N>, T, N>), grid, block, 0, stream, p);
+    } else if (plan.block <= 256) {
+      hipLaunchKernelGGL((k_sample_major<F<T, N>, T, N, 256>), grid, block, 0, stream, p);
+    } else if constexpr (N <= kAnyMaxDims) {
+      hipLaunchKernelGGL((k_sample_major<F<T, N>, T, N, 1024>), grid, block, 0, stream, p);
     } else {
-      hipLaunchKernelGGL((k_sample_major<F<T, N>, T, N>), grid, block, 0, stream, p);
+      return hipErrorInvalidValue;  // the planner refuses such blocks
     }
     return hipGetLastError();
   }
