@@ -168,8 +168,9 @@ uint64_t cdiv(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 // wave; the sample range is then cut into enough pieces that the launch holds
 // ~16 waves per wave slot (so the last round of blocks is a small fraction
 // of the run), each piece keeping >= 64 groups (256 samples) per lane.
-// Otherwise sample-major with enough blocks per point for ~4 waves per slot
-// and >= 16 groups per lane.
+// So are mid-sized FP64 grids where that is expected to be faster
+// (mid_grid_pieces).  Otherwise sample-major with enough blocks per point for ~4
+// waves per slot and >= 16 groups per lane.
 constexpr uint64_t kMaxGridX = (uint64_t)1 << 30;
 constexpr int kMaxSplits = 65535;
 constexpr uint64_t kMaxWorkspace = (uint64_t)8 << 30;
@@ -180,6 +181,35 @@ constexpr uint64_t kDefaultChunk = (uint64_t)1 << 24;  // points per chunk of a 
 constexpr uint64_t kMaxBytes = (uint64_t)1 << 56;
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
+// FP64 grids that do not fill the device with one wave per 64 points: the
+// number of sample pieces with which the point-major layout is expected to be
+// faster than the sample-major one, or 0.  Point-major pays once per wave and
+// piece (set-up, moments, a share of the merge pass: about 6 groups of four
+// samples) but its lanes all work; sample-major pays per block of one point
+// (set-up and two block sums, about 4 groups) and leaves lanes idle in the last
+// row of groups.  Both are counted in group times per SIMD, with fewer than 1.7
+// waves per SIMD no faster than 1.7; the merge pass costs a launch (about 38 / N
+// group times).  Pieces give each SIMD about five waves, of at least 16 groups.
+// Measured (sample- -> point-major, back-to-back calls): 20467 points x 2049
+// samples N = 12 319 -> 183 us, 40000 x 257 N = 4 121 -> 32, 30000 x 1024 N = 8
+// 234 -> 107, 15000 x 2050 N = 2 84 -> 50; 500 x 16384 N = 4 stays sample-major
+// (its kernel takes 23 us, point-major 24 and the merge).  The FP32 path keeps the
+// sample-major layout for such grids: its sums are shifted by a lane's first
+// sample, so another layout moves a result by FP32 roundings.
+uint64_t mid_grid_pieces(uint64_t G, uint64_t groups, int N, uint64_t simds) {
+  if (G < 64 || G >= simds * 64) return 0;
+  const uint64_t waves = cdiv(G, 64);
+  uint64_t splits = cdiv(5 * simds, waves);
+  splits = std::min<uint64_t>(splits, std::max<uint64_t>(1, groups / 16));
+  splits = std::min<uint64_t>(splits, 256);
+  auto per_simd = [&](uint64_t w) { return std::max(1.7, (double)w / (double)simds); };
+  const double pm = ((double)cdiv(groups, splits) + 6.0) * per_simd(waves * splits) +
+                    (splits > 1 ? 38.0 / N : 0.0);
+  const uint64_t sm_waves = std::min<uint64_t>(4, cdiv(groups, 64));
+  const double sm = ((double)cdiv(groups, 256) + 4.0) * per_simd(G * sm_waves);
+  return pm < 0.85 * sm ? splits : 0;
+}
+
 zmc_status make_plan(const zmc_scan_desc* d, uint64_t G, const zmc_launch_opts* o, zmc::Plan* pl) {
   int cu = (o && o->cu_count > 0) ? o->cu_count : 0;
   if (cu == 0) {
@@ -189,7 +219,12 @@ zmc_status make_plan(const zmc_scan_desc* d, uint64_t G, const zmc_launch_opts* 
   const uint64_t slots = (uint64_t)cu * 4 * 8;  // wave slots: 4 SIMDs x 8 waves
   const uint64_t groups = cdiv(d->samples, 4);
   int mode = o ? o->mode : ZMC_MODE_AUTO;
-  if (mode == ZMC_MODE_AUTO)
+  uint64_t mid_splits = 0;  // > 0: point-major pieces of a mid-sized FP64 grid
+  if (mode == ZMC_MODE_AUTO && (!o || (o->block <= 0 && o->splits <= 0)) && d->precision == ZMC_FP64)
+    mid_splits = mid_grid_pieces(G, groups, d->N, (uint64_t)cu * 4);
+  if (mid_splits > 0)
+    mode = ZMC_MODE_POINT_MAJOR;
+  else if (mode == ZMC_MODE_AUTO)
     mode = (G >= (uint64_t)cu * 4 * 64) ? ZMC_MODE_POINT_MAJOR : ZMC_MODE_SAMPLE_MAJOR;
   if (mode != ZMC_MODE_POINT_MAJOR && mode != ZMC_MODE_SAMPLE_MAJOR)
     return fail(ZMC_E_INVALID, "unknown mode %d", mode);
@@ -200,7 +235,7 @@ zmc_status make_plan(const zmc_scan_desc* d, uint64_t G, const zmc_launch_opts* 
     return fail(ZMC_E_INVALID, "point-major blocks hold at most 256 threads");
   if (d->N > zmc::kAnyMaxDims && block > 256)
     return fail(ZMC_E_INVALID, "blocks of scans with N > %d hold at most 256 threads", zmc::kAnyMaxDims);
-  uint64_t splits = (o && o->splits > 0) ? (uint64_t)o->splits : 0;
+  uint64_t splits = (o && o->splits > 0) ? (uint64_t)o->splits : mid_splits;
   if (splits == 0) {
     if (mode == ZMC_MODE_POINT_MAJOR) {
       const uint64_t waves = cdiv(G, 64);
@@ -265,10 +300,12 @@ void fill_params(const zmc_scan_desc* d, uint64_t G, const zmc::Plan& pl, const 
   p->family = d->family;
   p->fast_counter =
       (g_base + G <= ((uint64_t)1 << 32) && pl.groups * (uint64_t)d->N <= ((uint64_t)1 << 32)) ? 1 : 0;
+  p->small_index = g_base + G <= ((uint64_t)1 << 32) ? 1 : 0;
   int64_t off = 0;
   uint64_t stride = 1;
   for (int l = d->M - 1; l >= 0; --l) {
     p->axis_stride[l] = stride;
+    p->axis_inv[l] = 1.0 / (double)stride;
     stride *= (uint64_t)d->axis_len[l];
   }
   for (int l = 0; l < d->M; ++l) {

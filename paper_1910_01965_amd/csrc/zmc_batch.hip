@@ -24,6 +24,10 @@ using zmc::ok;
 
 namespace zmc {
 
+// Word blocks per lane of a point-major tile that is short beside any batch
+// (about 0.3 ms in FP64).
+constexpr uint64_t kShortTileBlocks = 1024;
+
 // The tiled decomposition of one scan (batches and the server): a function of
 // the scan and the tuned table only, so a scan's results do not depend on
 // what else runs with it.  Point-major tiles hold 256 consecutive points and
@@ -38,7 +42,13 @@ zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_over
   const int64_t sm_groups = sm_groups_override > 0 ? sm_groups_override : t.sm_groups;
   const int64_t pm_min = pm_min_override > 0 ? pm_min_override : t.pm_min_points;
   const uint64_t groups = (d->samples + 3) / 4;
-  pl->mode = (G >= (uint64_t)pm_min) ? ZMC_MODE_POINT_MAJOR : ZMC_MODE_SAMPLE_MAJOR;
+  // FP64 scans of few samples: a sample-major tile costs its block about four
+  // rows of groups besides its own (set-up, two block sums), so grids of at least
+  // one block of points whose whole sample range is a short tile are point-major
+  // too (as in the plans of single scans, the FP32 path keeps its layout)
+  const bool short_fp64 = pm_min_override <= 0 && d->precision == ZMC_FP64 && G >= (uint64_t)kTileBlock &&
+                          groups * (uint64_t)d->N <= kShortTileBlocks && (int64_t)groups <= pm_groups;
+  pl->mode = (G >= (uint64_t)pm_min || short_fp64) ? ZMC_MODE_POINT_MAJOR : ZMC_MODE_SAMPLE_MAJOR;
   pl->block = kTileBlock;
   const uint64_t gpt = (uint64_t)(pl->mode == ZMC_MODE_POINT_MAJOR ? pm_groups : sm_groups);
   uint64_t splits = (groups + gpt - 1) / gpt;

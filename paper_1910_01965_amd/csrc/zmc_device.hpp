@@ -41,10 +41,13 @@ struct ScanParams {
   uint64_t point_blocks; // ceil(G / block) (point-major)
   int32_t M, N, splits, family;
   int32_t fast_counter;  // 1 when every word block b and global index g is < 2^32
+  int32_t small_index;   // 1 when every global index g is < 2^32
   int32_t n_params;      // user integrands: entries of params in use
+  int32_t pad;
   int64_t axis_len[kMaxParams];
   int64_t axis_off[kMaxParams];
   uint64_t axis_stride[kMaxParams];  // prod of the lengths of later axes
+  double axis_inv[kMaxParams];       // 1 / axis_stride
   double lo[kMaxDims], hi[kMaxDims];
   double vol;
   double params[kMaxUserParams];
@@ -607,11 +610,35 @@ template <class Fam> __device__ __forceinline__ void load_tables() {
   if constexpr (UsesExp2Table<Fam>::value) exp2_table_load();
 }
 
-// Parameter x_l of grid point g (C order: stride_l = prod_{j>l} L_j).
+// Parameter x_l of grid point g (C order: stride_l = prod_{j>l} L_j), for the
+// FP32 user integrands, which keep the code they had (see Phased).
 __device__ __forceinline__ double param_x(const ScanParams& p, uint64_t g, int l) {
   const uint64_t i = (g / p.axis_stride[l]) % (uint64_t)p.axis_len[l];
   return p.axis[p.axis_off[l] + (int64_t)i];
 }
+
+// Parameters x_0, x_1, ... of grid point g in turn (C order: stride_l = prod_{j>l}
+// L_j): with q_l = floor(g / stride_l), index i_l = q_l - q_(l-1) L_l.  For g < 2^32
+// floor((g + 1/2) (1 / stride)) in FP64 is exact: the quotient stays 1 / (2 stride)
+// away from an integer, far above the product's error of q 2^-52.  Six
+// instructions a parameter instead of two 64-bit divisions of some 130 each
+// (10^7 points x 16 samples over three parameters: 167 -> 145 us).
+struct ParamCursor {
+  const ScanParams& p;
+  uint64_t g;
+  double gh;
+  uint32_t q = 0;
+  __host__ __device__ __forceinline__ ParamCursor(const ScanParams& sp, uint64_t gg)
+      : p(sp), g(gg), gh((double)(uint32_t)gg + 0.5) {}
+  __host__ __device__ __forceinline__ uint64_t index(int l) {
+    if (!p.small_index) return (g / p.axis_stride[l]) % (uint64_t)p.axis_len[l];
+    const uint32_t ql = (uint32_t)(gh * p.axis_inv[l]);
+    const uint32_t i = ql - q * (uint32_t)p.axis_len[l];
+    q = ql;
+    return i;
+  }
+  __device__ __forceinline__ double next(int l) { return p.axis[p.axis_off[l] + (int64_t)index(l)]; }
+};
 
 // ---------------------------------------------------------------------------
 // Integrand families.  Each one holds the per-point constants (set up once
@@ -631,7 +658,8 @@ template <typename T, int N> struct SinSum {
   T sx;        // FP64: sum of x; FP32: sum x + sum B (A and sx in revolutions)
   __device__ void setup(const ScanParams& p, uint64_t g) {
     double s = 0.0, sb = 0.0;
-    for (int l = 0; l < p.M; ++l) s += param_x(p, g, l);
+    ParamCursor x(p, g);
+    for (int l = 0; l < p.M; ++l) s += x.next(l);
 #pragma unroll
     for (int k = 0; k < N; ++k) {
       double a, b;
@@ -692,9 +720,10 @@ template <typename T, int N> struct Gauss {
   __device__ void setup(const ScanParams& p, uint64_t g) {
     double x[N];
     bool fold = true;
+    ParamCursor cursor(p, g);
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-      x[k] = (k < p.M) ? param_x(p, g, k) : 1.0;
+      x[k] = (k < p.M) ? cursor.next(k) : 1.0;
       fold = fold && x[k] >= 0.0 && x[k] <= 0x1.fffffffffffffp+1023;
     }
 #pragma unroll
@@ -753,11 +782,12 @@ template <int N> struct CosExp<float, N> {
       B[k] = (float)b;
       if (k >= 2) sb += b;
     }
-    x1 = (float)(param_x(p, g, 0) * turn);
-    x2 = (float)(param_x(p, g, 1) * turn);
-    const double x3 = param_x(p, g, 2);
+    ParamCursor x(p, g);
+    x1 = (float)(x.next(0) * turn);
+    x2 = (float)(x.next(1) * turn);
+    const double x3 = x.next(2);
     nx3sq = (float)(-(x3 * x3) * kLog2e);
-    x4 = (float)param_x(p, g, 3);
+    x4 = (float)x.next(3);
     rest = (float)(sb * turn);
   }
   __device__ __forceinline__ float value(const float* t) const {
@@ -797,7 +827,8 @@ template <int N> struct CosExp<double, N> {
         sb += b[k];
       }
     }
-    const double x1 = param_x(p, g, 0), x2 = param_x(p, g, 1), x3 = param_x(p, g, 2);
+    ParamCursor x(p, g);
+    const double x1 = x.next(0), x2 = x.next(1), x3 = x.next(2);
     P[0] = x1 * kInv2Pi * a[0];
     P[1] = x2 * kInv2Pi * a[1];
     C = turns_fraction(x1 * b[0]) + turns_fraction(x2 * b[1]) + turns_fraction(sb);
@@ -806,7 +837,7 @@ template <int N> struct CosExp<double, N> {
     F = nx3sq * b[0];
     A2 = a[1];
     B2 = b[1];
-    x4 = param_x(p, g, 3);
+    x4 = x.next(3);
   }
   __device__ __forceinline__ double value(const double* t) const {
     double ph = C;

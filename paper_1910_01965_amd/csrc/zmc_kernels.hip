@@ -7,9 +7,8 @@ namespace zmc {
 
 // Second pass: merge the split partials of each point in split order.
 __global__ __launch_bounds__(256) void k_merge_splits(ScanParams p) {
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < p.G; g += stride)
-    merge_point(p, g);
+  __shared__ double lds[3 * 256];
+  merge_body(p, lds);
 }
 
 // Zeroes the batch's tile counters (a kernel rather than a memset, so that
@@ -22,10 +21,8 @@ __global__ void k_reset_counters(uint32_t* counters, int n) {
 // blockIdx.y selects the scan.
 __global__ __launch_bounds__(256) void k_merge_batch(const ScanParams* __restrict__ scans,
                                                      const uint32_t* __restrict__ merge_scans) {
-  const ScanParams& p = scans[merge_scans[blockIdx.y]];
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < p.G; g += stride)
-    merge_point(p, g);
+  __shared__ double lds[3 * 256];
+  merge_body(scans[merge_scans[blockIdx.y]], lds);
 }
 
 __global__ void k_debug_words(uint64_t seed, uint64_t g, uint64_t w0, int64_t count,
@@ -177,7 +174,8 @@ hipError_t launch_scan(const ScanParams& p, const Plan& plan, int precision, hip
 }
 
 hipError_t launch_merge_splits(const ScanParams& p, hipStream_t stream) {
-  uint64_t blocks = (p.G + 255) / 256;
+  const uint64_t per = p.splits < kMergeTreeSplits ? 256 : 16;  // points a block
+  uint64_t blocks = (p.G + per - 1) / per;
   if (blocks > (1u << 20)) blocks = 1u << 20;
   hipLaunchKernelGGL(k_merge_splits, dim3((unsigned)blocks), dim3(256), 0, stream, p);
   return hipGetLastError();
@@ -215,8 +213,8 @@ hipError_t launch_reset_counters(uint32_t* counters, int n, hipStream_t stream) 
 hipError_t launch_merge_batch(const ScanParams* scans, const uint32_t* merge_scans, int n_merge,
                               uint64_t max_points, hipStream_t stream) {
   if (n_merge <= 0) return hipSuccess;
-  uint64_t bx = (max_points + 255) / 256;
-  if (bx > 4096) bx = 4096;
+  uint64_t bx = (max_points + 15) / 16;
+  if (bx > 1024) bx = 1024;
   hipLaunchKernelGGL(k_merge_batch, dim3((unsigned)bx, (unsigned)n_merge), dim3(256), 0, stream,
                      scans, merge_scans);
   return hipGetLastError();

@@ -30,8 +30,9 @@ struct UserFamily {
       A[k] = (T)a;
       B[k] = (T)b;
     }
+    ParamCursor cursor(p, g);
 #pragma unroll
-    for (int l = 0; l < M; ++l) x[l] = (T)param_x(p, g, l);
+    for (int l = 0; l < M; ++l) x[l] = (T)(kPhased ? cursor.next(l) : param_x(p, g, l));
 #pragma unroll
     for (int i = 0; i < kMaxUserParams; ++i) q[i] = (T)p.params[i];
   }
