@@ -28,6 +28,13 @@ namespace zmc {
 // (about 0.3 ms in FP64).
 constexpr uint64_t kShortTileBlocks = 1024;
 
+// Tiles that a scan's grid is cut into, its sample range included, and the
+// shortest pieces for that: 8192 tiles are about five rounds of the device's
+// resident blocks, and in 128 groups the set-up is 3 %.
+// The partials of such a scan stay below 16 B x 256 x 2 x 8192 = 64 MiB.
+constexpr uint64_t kFineTiles = 8192;
+constexpr uint64_t kFineGroups = 128;
+
 // The tiled decomposition of one scan (batches and the server): a function of
 // the scan and the tuned table only, so a scan's results do not depend on
 // what else runs with it.  Point-major tiles hold 256 consecutive points and
@@ -36,7 +43,7 @@ constexpr uint64_t kShortTileBlocks = 1024;
 // partials of one scan are kept below 2 GiB by lengthening its pieces.
 zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_override,
                       int64_t sm_groups_override, int64_t pm_min_override, Plan* pl,
-                      uint64_t* tiles) {
+                      uint64_t* tiles, uint64_t max_partial_bytes) {
   const TuneEntry t = tune_lookup(d->family, d->precision, d->N);
   const int64_t pm_groups = pm_groups_override > 0 ? pm_groups_override : t.pm_groups;
   const int64_t sm_groups = sm_groups_override > 0 ? sm_groups_override : t.sm_groups;
@@ -55,14 +62,29 @@ zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_over
   while (splits > 1 && 16.0 * (double)splits * (double)G > (double)kMaxPartialBytesPerScan)
     splits = (splits + 1) / 2;
   if (splits > 0x7FFFFFFFull) return fail(ZMC_E_UNSUPPORTED, "too many sample pieces");
-  const uint64_t gps = (groups + splits - 1) / splits;
+  uint64_t gps = (groups + splits - 1) / splits;
   splits = (groups + gps - 1) / gps;
+  // A lane walks its piece's samples one after another, so a tile of the table's
+  // length (up to 8192 groups) lasts milliseconds, which the scans of a small mix
+  // wait for while the device drains: FP64 grids of fewer than kFineTiles blocks
+  // of points get more, shorter pieces.  FP32 keeps the table's pieces: another cut
+  // moves its results by roundings of the lanes' sums (up to 8e-9 of sigma).
+  const uint64_t point_blocks = (G + kTileBlock - 1) / kTileBlock;
+  if (pl->mode == ZMC_MODE_POINT_MAJOR && pm_groups_override <= 0 && d->precision == ZMC_FP64 &&
+      point_blocks < kFineTiles) {
+    const uint64_t fine = std::min<uint64_t>((kFineTiles + point_blocks - 1) / point_blocks,
+                                             groups / kFineGroups);
+    if (fine > splits && 16 * fine * G <= max_partial_bytes) {
+      gps = (groups + fine - 1) / fine;
+      splits = (groups + gps - 1) / gps;
+    }
+  }
   const zmc_status pst = check_pieces(groups, gps, splits);
   if (pst != ZMC_OK) return pst;
   pl->splits = (int)splits;
   pl->groups = groups;
   pl->gps = gps;
-  pl->point_blocks = (G + kTileBlock - 1) / kTileBlock;
+  pl->point_blocks = point_blocks;
   pl->grid_x = 0;
   pl->workspace_bytes = splits > 1 ? 16 * splits * G : 0;
   *tiles = (pl->mode == ZMC_MODE_POINT_MAJOR ? pl->point_blocks : G) * splits;

@@ -54,7 +54,7 @@ constexpr int kTileBlock = 256;
 constexpr uint64_t kMaxPartialBytesPerScan = (uint64_t)2 << 30;
 zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_override,
                       int64_t sm_groups_override, int64_t pm_min_override, Plan* pl,
-                      uint64_t* tiles);
+                      uint64_t* tiles, uint64_t max_partial_bytes = ~(uint64_t)0);
 const char* tune_source();
 hipError_t batch_occupancy(int precision, int family, int N, int* blocks_per_cu);
 hipError_t launch_batch_variant(int precision, int family, int N, const ScanParams* scans,

@@ -715,7 +715,11 @@ zmc_status zmc_server_submit(zmc_server* s, const zmc_scan_desc* desc, const dou
   r->d_f = d_f;
   r->d_sigma = d_sigma;
   r->G = G;
-  st = zmc::plan_tiles(&r->desc, G, 0, 0, 0, &r->plan, &r->total_tiles);
+  // a finer cut than the tuned table's must not make a request too large for the
+  // whole budget
+  const uint64_t staged = align_up(8 * r->staged_doubles);
+  st = zmc::plan_tiles(&r->desc, G, 0, 0, 0, &r->plan, &r->total_tiles,
+                       s->opts.hbm_budget_bytes > staged ? s->opts.hbm_budget_bytes - staged : 0);
   if (st != ZMC_OK) return st;
   r->tile_samples = (uint64_t)std::max(
       1.0, (double)G * (double)desc->samples / (double)std::max<uint64_t>(1, r->total_tiles));
