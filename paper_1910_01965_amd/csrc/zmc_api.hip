@@ -276,6 +276,7 @@ zmc_status make_plan(const zmc_scan_desc* d, uint64_t G, const zmc_launch_opts* 
   const uint64_t gx = (mode == ZMC_MODE_POINT_MAJOR) ? pl->point_blocks : G;
   pl->grid_x = gx < kMaxGridX ? gx : kMaxGridX;
   pl->workspace_bytes = splits > 1 ? 16 * splits * G : 0;
+  pl->sm_points = 1;
   zmc::log(2, "plan: G=%llu n=%llu N=%d %s block=%d splits=%llu groups/piece=%llu blocks=%llu "
            "workspace=%llu B", (unsigned long long)G, (unsigned long long)d->samples, d->N,
            mode == ZMC_MODE_POINT_MAJOR ? "point-major" : "sample-major", block,
@@ -292,6 +293,7 @@ void fill_params(const zmc_scan_desc* d, uint64_t G, const zmc::Plan& pl, const 
   p->n = d->samples;
   p->n_groups = pl.groups;
   p->gps = pl.gps;
+  p->sm_points = pl.sm_points;
   p->seed = d->seed;
   p->point_blocks = pl.point_blocks;
   p->M = d->M;

@@ -87,7 +87,20 @@ zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_over
   pl->point_blocks = point_blocks;
   pl->grid_x = 0;
   pl->workspace_bytes = splits > 1 ? 16 * splits * G : 0;
-  *tiles = (pl->mode == ZMC_MODE_POINT_MAJOR ? pl->point_blocks : G) * splits;
+  // Sample-major tiles of short pieces take several points (explicit tile lengths
+  // keep one): as many as give each of the block's waves a piece of its own, and up
+  // to 16 points, 32 waves' groups in all, while the scan keeps 512 tiles (a mix of
+  // 12 FP64 scans of up to 9600 points: 498 us without that bound, 388 with one
+  // point a tile).
+  pl->sm_points = 1;
+  if (sm_groups_override <= 0) {
+    const uint64_t waves = std::max<uint64_t>(1, (gps + 63) / 64);  // of one point's piece
+    const uint64_t teams = waves >= 3 ? 1 : 4 / waves;
+    const uint64_t most = std::min<uint64_t>(std::min<uint64_t>(16, 32 / std::min<uint64_t>(waves, 32)), G / 512);
+    pl->sm_points = (uint32_t)std::max(teams, most);
+  }
+  const uint64_t sm_tiles = (G + pl->sm_points - 1) / pl->sm_points;
+  *tiles = (pl->mode == ZMC_MODE_POINT_MAJOR ? pl->point_blocks : sm_tiles) * splits;
   return ZMC_OK;
 }
 
@@ -223,9 +236,9 @@ zmc_status plan_batch(const zmc_scan_desc* scans, int32_t n, const zmc_batch_opt
           vec.push_back(TileCost{zmc::Tile{(uint32_t)i, (uint32_t)s, first}, lanes * samples * work});
         }
       } else {
-        for (uint64_t g = 0; g < sp.G; ++g)
+        for (uint64_t g = 0; g < sp.G; g += pl.sm_points)
           vec.push_back(TileCost{zmc::Tile{(uint32_t)i, (uint32_t)s | zmc::kTileSampleMajor, g},
-                                 samples * work});
+                                 std::min<uint64_t>(pl.sm_points, sp.G - g) * samples * work});
       }
     }
   }

@@ -43,7 +43,7 @@ struct ScanParams {
   int32_t fast_counter;  // 1 when every word block b and global index g is < 2^32
   int32_t small_index;   // 1 when every global index g is < 2^32
   int32_t n_params;      // user integrands: entries of params in use
-  int32_t pad;
+  uint32_t sm_points;    // points of a sample-major tile (batches, server)
   int64_t axis_len[kMaxParams];
   int64_t axis_off[kMaxParams];
   uint64_t axis_stride[kMaxParams];  // prod of the lengths of later axes

@@ -20,6 +20,7 @@ struct Plan {
   uint64_t grid_x;      // blocks along x (point blocks or points, capped)
   uint64_t point_blocks;
   uint64_t workspace_bytes;
+  uint32_t sm_points;   // points of a sample-major tile (plan_tiles)
 };
 
 hipError_t launch_scan(const ScanParams& p, const Plan& plan, int precision, hipStream_t stream,

@@ -129,73 +129,82 @@ __device__ __forceinline__ double strided_groups(const Fam& fam, const Gen& gen,
   return count;
 }
 
-// One sample-major tile: the whole block works on grid point g (local index;
-// its global index is p.g_base + g) over sample piece sp (lane t takes
-// groups j0 + t, j0 + t + T, ...), then merges its lanes: the mean of all
+// Sample-major work on grid point g (local index; its global index is p.g_base +
+// g) over sample piece sp by the `waves` waves of the block from wave w0 on: lane
+// t of them takes groups j0 + t, j0 + t + T, ... (T: the lanes of the whole block;
+// fewer waves than the block's are used for pieces of at most as many groups as
+// they have lanes).  Then the lanes are merged: the mean of all
 // samples from the lanes' sums, then M2 = sum_lanes (M2_lane + n_lane (mean_lane -
 // mean)^2).  Two sums of one double over the block replace a tree of pairwise
 // merges of three doubles, each with a division (about 1.3 us of a block's
 // time; a 10^4-point FP64 scan of 1024 samples, N = 4: 86 -> 55 us).
-// Every thread of the block must call it (it synchronises); `lds` holds 3 x 16
-// doubles.
+// Every thread of the block must call it, those with no point to work on with
+// `active` false (it synchronises unless `waves` is 1); `lds` holds 3 x 16 doubles.
 template <class Fam, typename T, int N>
-__device__ __forceinline__ void sm_tile(const ScanParams& p, uint64_t g, uint64_t sp, double* lds) {
+__device__ __forceinline__ void sm_work(const ScanParams& p, uint64_t g, uint64_t sp, double* lds,
+                                        unsigned w0, unsigned waves, bool active) {
+  const unsigned lane = threadIdx.x - 64 * w0;
   const uint64_t j0 = sp * p.gps;
   const uint64_t j1 = (j0 + p.gps < p.n_groups) ? j0 + p.gps : p.n_groups;
   const uint64_t last = p.n_groups - 1;
   const int tail = (int)(p.n - 4 * last);  // samples in the scan's last group
-  const unsigned waves = blockDim.x >> 6;
   const uint64_t len = j1 - j0;
   const uint64_t rows = (len + blockDim.x - 1) / blockDim.x;
-  const bool in_last = threadIdx.x < (unsigned)(len - (rows - 1) * blockDim.x);
-  Fam fam;
-  fam.setup(p, p.g_base + g);
+  const bool in_last = lane < (unsigned)(len - (rows - 1) * blockDim.x);
   LaneAcc<T> acc;
   acc.init((T)0);
   double count = 0.0;
-  with_form(fam, [&](const auto& f) {
-    using F = std::decay_t<decltype(f)>;
-    if constexpr (Phased<F>::value) {
-      if (p.fast_counter) {
-        const GenSampleMajorPhased gen{philox_point((uint32_t)(p.g_base + g), p.seed)};
-        count = strided_groups<F, T, N>(f, gen, j0 + threadIdx.x, blockDim.x, rows, in_last, last, tail, acc);
-        return;
-      }
-    }
-    const GenAny gen{p.g_base + g, p.seed};
-    if constexpr (Phased<F>::value) {
-      count = strided_groups<F, T, N>(f, gen, j0 + threadIdx.x, blockDim.x, rows, in_last, last, tail, acc);
-    } else {
-      for (uint64_t j = j0 + threadIdx.x; j < j1; j += blockDim.x) {
-        T v[4];
-        eval_group<F, T, N>(f, j, gen, v);
-        if (count == 0.0) acc.init(v[0]);  // shift by the lane's first sample
-        if (j == last && tail != 4) {
-          acc.add_partial(v, tail);
-          count += (double)tail;
-        } else {
-          acc.add4(v);
-          count += 4.0;
+  if (active) {
+    Fam fam;
+    fam.setup(p, p.g_base + g);
+    with_form(fam, [&](const auto& f) {
+      using F = std::decay_t<decltype(f)>;
+      if constexpr (Phased<F>::value) {
+        if (p.fast_counter) {
+          const GenSampleMajorPhased gen{philox_point((uint32_t)(p.g_base + g), p.seed)};
+          count = strided_groups<F, T, N>(f, gen, j0 + lane, blockDim.x, rows, in_last, last, tail, acc);
+          return;
         }
       }
-    }
-  });
+      const GenAny gen{p.g_base + g, p.seed};
+      if constexpr (Phased<F>::value) {
+        count = strided_groups<F, T, N>(f, gen, j0 + lane, blockDim.x, rows, in_last, last, tail, acc);
+      } else {
+        for (uint64_t j = j0 + lane; j < j1; j += blockDim.x) {
+          T v[4];
+          eval_group<F, T, N>(f, j, gen, v);
+          if (count == 0.0) acc.init(v[0]);  // shift by the lane's first sample
+          if (j == last && tail != 4) {
+            acc.add_partial(v, tail);
+            count += (double)tail;
+          } else {
+            acc.add4(v);
+            count += 4.0;
+          }
+        }
+      }
+    });
+  }
   const Moments m = to_moments(acc, count);
   const double n = (double)split_samples(p.n, p.n_groups, p.gps, sp);
+  double mean = wave_sum(m.n * m.mean);
   const unsigned w = threadIdx.x >> 6;
-  const double s1 = wave_sum(m.n * m.mean);
-  if ((threadIdx.x & 63u) == 0) lds[w] = s1;
-  __syncthreads();
-  double mean = lds[0];
-  for (unsigned i = 1; i < waves; ++i) mean += lds[i];
+  if (waves > 1) {
+    if ((threadIdx.x & 63u) == 0) lds[w] = mean;
+    __syncthreads();
+    mean = lds[w0];
+    for (unsigned i = 1; i < waves; ++i) mean += lds[w0 + i];
+  }
   mean /= n;
   const double d = m.mean - mean;
-  const double s2 = wave_sum(m.n > 0.0 ? m.m2 + m.n * d * d : 0.0);
-  if ((threadIdx.x & 63u) == 0) lds[16 + w] = s2;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double m2 = lds[16];
-    for (unsigned i = 1; i < waves; ++i) m2 += lds[16 + i];
+  double m2 = wave_sum(m.n > 0.0 ? m.m2 + m.n * d * d : 0.0);
+  if (waves > 1) {
+    if ((threadIdx.x & 63u) == 0) lds[16 + w] = m2;
+    __syncthreads();
+    m2 = lds[16 + w0];
+    for (unsigned i = 1; i < waves; ++i) m2 += lds[16 + w0 + i];
+  }
+  if (lane == 0 && active) {
     if (p.splits == 1) {
       finalize(p, g, Moments{n, mean, m2});
     } else {
@@ -203,7 +212,35 @@ __device__ __forceinline__ void sm_tile(const ScanParams& p, uint64_t g, uint64_
       p.part_m2[sp * p.G + g] = m2;
     }
   }
-  __syncthreads();
+  if (waves > 1) __syncthreads();
+}
+
+// The whole block on one point.
+template <class Fam, typename T, int N>
+__device__ __forceinline__ void sm_tile(const ScanParams& p, uint64_t g, uint64_t sp, double* lds) {
+  sm_work<Fam, T, N>(p, g, sp, lds, 0, blockDim.x >> 6, true);
+}
+
+// A sample-major tile of a batch: `p.sm_points` consecutive points from `first`
+// over sample piece sp, by a block of four waves.  A piece that fits the lanes of
+// one or two waves gives each wave, or each pair, its own points.  A tile of one
+// point costs its block a queue pop, the tile and scan records and the set-up one
+// after another, latency that short pieces do not cover: a mix of 30 FP32 scans
+// takes 2.63 ms, and took 4.27 with one point a tile.
+template <class Fam, typename T, int N>
+__device__ __forceinline__ void sm_tile_points(const ScanParams& p, uint64_t first, uint64_t sp, double* lds) {
+  const uint64_t j0 = sp * p.gps;
+  const uint64_t j1 = (j0 + p.gps < p.n_groups) ? j0 + p.gps : p.n_groups;
+  const unsigned waves = j1 - j0 <= 64 ? 1 : j1 - j0 <= 128 ? 2 : 4;
+  const unsigned teams = 4 / waves, w = threadIdx.x >> 6;
+  const unsigned team = __builtin_amdgcn_readfirstlane(w / waves);
+  const uint64_t left = p.G - first;
+  const unsigned count = left < p.sm_points ? (unsigned)left : p.sm_points;
+  for (unsigned i = 0; i < count; i += teams) {
+    const unsigned at = i + team;
+    const bool active = at < count;
+    sm_work<Fam, T, N>(p, first + (active ? at : 0), sp, lds, team * waves, waves, active);
+  }
 }
 
 // Merge of point g's pieces s0 .. s1-1 in order; loads run four pieces ahead of
@@ -294,17 +331,24 @@ __device__ __forceinline__ void batch_body(const ScanParams* __restrict__ scans,
                                            uint32_t end, uint32_t* counter, uint32_t* next,
                                            double* lds) {
   load_tables<Fam>();
+  // far from the end of the table thread 0 pops the next tile while the block
+  // runs the last one; near it a tile that waits for a busy block would keep the
+  // device waiting (12 small FP64 scans: 507 us when it did, 388 without)
+  uint32_t popped = 0;
+  bool have = false;
   for (;;) {
     __syncthreads();  // the previous tile is done with `next` and `lds`
-    if (threadIdx.x == 0) *next = begin + atomicAdd(counter, 1u);
+    if (threadIdx.x == 0) *next = have ? popped : begin + atomicAdd(counter, 1u);
     __syncthreads();
     const uint32_t t = *next;
     if (t >= end) break;
+    have = end - t > 4u * gridDim.x;
+    if (have && threadIdx.x == 0) popped = begin + atomicAdd(counter, 1u);
     const Tile tl = tiles[t];
     const ScanParams& p = scans[tl.scan];
     const uint64_t sp = tl.split_mode & ~kTileSampleMajor;
     if (tl.split_mode & kTileSampleMajor) {
-      sm_tile<Fam, T, N>(p, tl.first, sp, lds);
+      sm_tile_points<Fam, T, N>(p, tl.first, sp, lds);
     } else {
       pm_tile<Fam, T, N>(p, tl.first, sp);
     }

@@ -141,12 +141,12 @@ size_t align_up(size_t x) { return (x + 255) / 256 * 256; }
 
 zmc::Tile tile_of(const Request& r, uint64_t t) {
   const bool pm = r.plan.mode == ZMC_MODE_POINT_MAJOR;
-  const uint64_t per = pm ? r.plan.point_blocks : r.G;
+  const uint64_t per = pm ? r.plan.point_blocks : (r.G + r.plan.sm_points - 1) / r.plan.sm_points;
   const uint64_t split = t / per, i = t % per;
   zmc::Tile tl;
   tl.scan = (uint32_t)r.slot;
   tl.split_mode = (uint32_t)split | (pm ? 0u : zmc::kTileSampleMajor);
-  tl.first = pm ? i * zmc::kTileBlock : i;
+  tl.first = i * (pm ? (uint64_t)zmc::kTileBlock : (uint64_t)r.plan.sm_points);
   return tl;
 }
 

@@ -63,7 +63,7 @@ __device__ __forceinline__ void run_tile_any(const ScanParams& p, const Tile& tl
 #define ZMC_TILE_CASE(FAM, NN)                                  \
   case FAM##_ID * 32 + NN:                                      \
     if (sm)                                                     \
-      sm_tile<FAM<T, NN>, T, NN>(p, tl.first, sp, lds);         \
+      sm_tile_points<FAM<T, NN>, T, NN>(p, tl.first, sp, lds);  \
     else                                                        \
       pm_tile<FAM<T, NN>, T, NN>(p, tl.first, sp);              \
     break;
@@ -99,12 +99,16 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_batch_any(const
   __shared__ uint32_t next;
   __shared__ double lds[48];
   if constexpr (sizeof(T) == 8) exp2_table_load();
+  uint32_t popped = 0;  // as in batch_body
+  bool have = false;
   for (;;) {
     __syncthreads();
-    if (threadIdx.x == 0) next = begin + atomicAdd(counter, 1u);
+    if (threadIdx.x == 0) next = have ? popped : begin + atomicAdd(counter, 1u);
     __syncthreads();
     const uint32_t t = next;
     if (t >= end) break;
+    have = end - t > 4u * gridDim.x;
+    if (have && threadIdx.x == 0) popped = begin + atomicAdd(counter, 1u);
     const Tile tl = tiles[t];
     run_tile_any<T>(scans[tl.scan], tl, lds);
   }
