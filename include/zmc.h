@@ -199,7 +199,10 @@ zmc_status zmc_scan_device(const zmc_scan_desc* desc, const double* d_axis_vals,
  * from pinned staging into them on host threads ($ZMC_COPY_THREADS, 1..64,
  * default 8); outputs in pinned memory
  * (hipHostMalloc) take the copies directly.  Device memory: the lists plus
- * 2 x 16 B x chunk_points plus the chunk's split partials.  Synchronous.
+ * 2 x 16 B x chunk_points plus the chunk's split partials.  A scan of one chunk
+ * whose lists, f and sigma fit 4 MiB runs through a stream and pinned staging
+ * that the library keeps (at most four of each per device) and the workspace
+ * cache of zmc_scan_device.  Synchronous.
  * f and sigma must be host memory (ZMC_E_INVALID for device pointers). */
 zmc_status zmc_scan_chunked(const zmc_scan_desc* desc, double* f, double* sigma,
                             uint64_t chunk_points);
