@@ -52,9 +52,11 @@ zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_over
   // FP64 scans of few samples: a sample-major tile costs its block about four
   // rows of groups besides its own (set-up, two block sums), so grids of at least
   // one block of points whose whole sample range is a short tile are point-major
-  // too (as in the plans of single scans, the FP32 path keeps its layout)
+  // too (as in the plans of single scans, the FP32 path keeps its layout); the fewer
+  // tiles such a grid has, the shorter they must be, or a mix waits for them
   const bool short_fp64 = pm_min_override <= 0 && d->precision == ZMC_FP64 && G >= (uint64_t)kTileBlock &&
-                          groups * (uint64_t)d->N <= kShortTileBlocks && (int64_t)groups <= pm_groups;
+                          groups * (uint64_t)d->N <= std::min(kShortTileBlocks, G / 8) &&
+                          (int64_t)groups <= pm_groups;
   pl->mode = (G >= (uint64_t)pm_min || short_fp64) ? ZMC_MODE_POINT_MAJOR : ZMC_MODE_SAMPLE_MAJOR;
   pl->block = kTileBlock;
   const uint64_t gpt = (uint64_t)(pl->mode == ZMC_MODE_POINT_MAJOR ? pm_groups : sm_groups);
