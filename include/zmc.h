@@ -333,8 +333,8 @@ zmc_status zmc_integrand_destroy(zmc_integrand* integrand);
 /* ------------------------------------------------------------------------
  * Batched scans.  Many independent scans of uneven grid sizes, sample
  * counts, families and dimensions run as one unit of work: the planner cuts
- * every scan into tiles (256 grid points x one sample piece, or one point x
- * one sample piece for grids below the tuned threshold), with tile shapes
+ * every scan into tiles (256 grid points x one sample piece, or a few points
+ * x one sample piece for grids below the tuned threshold), with tile shapes
  * from the autotuned table (tune_table.txt next to the library, or
  * $ZMC_TUNE_TABLE); one persistent kernel per (family, precision, N)
  * variant drains its longest-first tile queue; a second pass merges split

@@ -39,8 +39,9 @@ constexpr uint64_t kFineGroups = 128;
 // the scan and the tuned table only, so a scan's results do not depend on
 // what else runs with it.  Point-major tiles hold 256 consecutive points and
 // `pm_groups` groups of four samples per lane; grids below `pm_min_points`
-// get sample-major tiles of `sm_groups` groups (all lanes together).  The
-// partials of one scan are kept below 2 GiB by lengthening its pieces.
+// get sample-major tiles of `sm_groups` groups (all lanes together) and a few
+// points.  The partials of one scan are kept below 2 GiB by lengthening its pieces;
+// FP64 pieces are cut finer only while the partials stay within max_partial_bytes.
 zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_override,
                       int64_t sm_groups_override, int64_t pm_min_override, Plan* pl,
                       uint64_t* tiles, uint64_t max_partial_bytes) {

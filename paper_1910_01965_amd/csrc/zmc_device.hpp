@@ -59,12 +59,12 @@ struct ScanParams {
 };
 
 // One unit of batched work: a point-major tile (256 consecutive grid points
-// of one scan over one sample piece) or a sample-major tile (one grid point,
-// one sample piece, the whole block).
+// of one scan over one sample piece) or a sample-major tile (ScanParams::sm_points
+// consecutive grid points, one sample piece, the whole block).
 struct Tile {
   uint32_t scan;        // index into the batch's scan table
   uint32_t split_mode;  // bits 0..30: sample piece; bit 31: 1 = sample-major
-  uint64_t first;       // point-major: first grid point; sample-major: the point
+  uint64_t first;       // point-major: first grid point; sample-major: its first point
 };
 
 constexpr uint32_t kTileSampleMajor = 0x80000000u;
