@@ -1,0 +1,31 @@
+"""Host builds of the FP64 integrands at the edges of their ranges (no GPU)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_1910_01965_amd", "csrc")
+
+
+def _run(name, tmp_path):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path / name)
+    subprocess.run([hipcc, "-x", "hip", "--offload-arch=gfx950", "-O2", "-I", CSRC,
+                    "-I", os.path.join(ROOT, "include"),
+                    os.path.join(HERE, "cpu_checks", name + ".cpp"), "-o", exe], check=True)
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0, out.stderr
+    return out.stdout.split()
+
+
+def test_sin_of_small_phases_keeps_its_relative_accuracy(tmp_path):
+    """Within the roundings of 1/(2 pi), of A and of the phase (N - 1 additions and
+    one fma) and the sine polynomial's own error."""
+    e1, e3, bad, out = _run("small_phase", tmp_path)
+    assert float(e1) < 1.0 and float(e3) < 1.0, (e1, e3)
+    assert int(bad) == 0 and int(out) == 0

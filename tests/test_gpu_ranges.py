@@ -1,0 +1,40 @@
+"""Scans at the edges of their value ranges, against the oracle."""
+import numpy as np
+import parity
+import pytest
+
+from oracle import oracle as zo
+from paper_1910_01965_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1910_01965_amd import zmc
+    zmc.load()
+    return torch
+
+
+def _check(spec, f, s, label):
+    f_ref, s_ref = zo.scan(spec)
+    parity.check(f.cpu().numpy(), s.cpu().numpy(), f_ref, s_ref, spec.samples, "fp64", label)
+
+
+# sin of a phase as small as the box: an absolute error of 1e-16 would be 1e-4 of f
+@pytest.mark.parametrize("N", [1, 3, 11])
+@pytest.mark.parametrize("w", [1e-3, 1e-6, 1e-12, 1e-17])
+def test_small_phases(w, N):
+    import torch
+    from paper_1910_01965_amd import zmc
+    spec = wl.ScanSpec("sin_sum", [np.zeros(130)], np.zeros(N), w * np.ones(N), 1031, 5, "fp64")
+    for mode in ("point_major", "sample_major"):
+        print("small phases", w, N, mode, flush=True)
+        f, s = zmc.scan(spec, mode=mode)
+        torch.cuda.synchronize()
+        _check(spec, f, s, f"w={w} N={N} {mode}")
+    (f, s), = zmc.scan_batch([spec])
+    _check(spec, f, s, f"w={w} N={N} batch")
