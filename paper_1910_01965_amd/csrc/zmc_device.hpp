@@ -556,20 +556,14 @@ __host__ __device__ __forceinline__ double exp2_parts(double m, double f) {
   return __builtin_ldexp(__builtin_fma(T, p, T), n >> 8);
 }
 
-// 2^(u / 256), for callers that scale the exponent by 256 in their constants.
-__host__ __device__ __forceinline__ double exp2_units(double u) {
-  u = __builtin_fmin(__builtin_fmax(u, -2100.0 * kExp2Scale), 2100.0 * kExp2Scale);
-  const double m = u + kRoundMagic;
-  return exp2_parts(m, u - (m - kRoundMagic));
-}
-
 // 2^t.  kNonPositive: the caller guarantees t <= 0 (or NaN), so only the lower
-// clamp is needed.
+// clamp is needed.  256 t is exact, so it takes no instruction of its own.
 template <bool kNonPositive = false>
 __host__ __device__ __forceinline__ double exp2_fp64(double t) {
   t = __builtin_fmax(t, -2100.0);
   if constexpr (!kNonPositive) t = __builtin_fmin(t, 2100.0);
-  return exp2_units(t * kExp2Scale);
+  const double m = __builtin_fma(t, kExp2Scale, kRoundMagic);
+  return exp2_parts(m, __builtin_fma(t, kExp2Scale, -(m - kRoundMagic)));
 }
 
 // e^(-q) = 2^(-q log2 e).  kNonNegative: q >= 0 (or NaN, which gives 0).
@@ -594,7 +588,8 @@ __host__ __device__ __forceinline__ double cos_turns(double r) {
 }
 
 // Radians to a fraction of a revolution in [-1/2, 1/2], without the rounding of
-// the whole revolutions: |error| below 2^-54 plus 2^-106 |s|.
+// the whole revolutions: |error| below 2^-54 plus 2^-106 |s| (host checks of the
+// phase reductions).
 __host__ __device__ __forceinline__ double turns_fraction(double s) {
   const double r = s * kInv2Pi;
   const double e = __builtin_fma(s, kInv2Pi, -r) + s * kInv2PiLo;
@@ -809,44 +804,40 @@ template <int N> struct CosExp<float, N> {
   }
 };
 
-// FP64: the phase and the exponent's first factor are linear in the variates,
-// so the point's parameters are folded into their coefficients at set-up:
-//   phase / (2 pi) = C + P1 t1 + P2 t2 + sum_{k>=3} A_k t_k  (C modulo 1)
-//   exponent = (E t1 + F) y2, y2 = A2 t2 + B2
-// i.e. N + 3 instructions instead of 2 N + 2 and the additions.
+// FP64: the box coordinates y1, y2 are formed first, each with one rounding, and
+// the exponent is their product.  Folding x3^2 into y1's map would save an
+// instruction, but lets its two coefficients' roundings meet where y1 is near 0:
+// on [-1, 0]^2 with x3 = 1000 the exponent of a sample is then off by 1e-11 instead of
+// 1e-14, and for |x3| from 7e152 an infinite offset hides a finite one.  Folding
+// x1, x2 and the other offsets into the phase's coefficients doubles the phase's
+// error on boxes around 0.
 template <int N> struct CosExp<double, N> {
   static constexpr int kMinDims = 2;
   static constexpr bool kExp2Table = true;
-  double P[N];        // P1, P2, then A_k, in revolutions
-  double C, E, F, A2, B2, x4;
-  __device__ void setup(const ScanParams& p, uint64_t g) {
-    double a[N], b[N], sb = 0.0;
+  double A[N], B[N];            // k >= 3: in revolutions (times 1/(2 pi))
+  double x1, x2, nx3sq, x4;     // x1, x2 in revolutions; nx3sq = -x3^2 log2(e)
+  __host__ __device__ void setup(const ScanParams& p, uint64_t g) {
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-      Unif<double>::affine(p.lo[k], p.hi[k], &a[k], &b[k]);
-      if (k >= 2) {
-        P[k] = a[k] * kInv2Pi;
-        sb += b[k];
-      }
+      double a, b;
+      Unif<double>::affine(p.lo[k], p.hi[k], &a, &b);
+      A[k] = k >= 2 ? a * kInv2Pi : a;
+      B[k] = k >= 2 ? b * kInv2Pi : b;
     }
     ParamCursor x(p, g);
-    const double x1 = x.next(0), x2 = x.next(1), x3 = x.next(2);
-    P[0] = x1 * kInv2Pi * a[0];
-    P[1] = x2 * kInv2Pi * a[1];
-    C = turns_fraction(x1 * b[0]) + turns_fraction(x2 * b[1]) + turns_fraction(sb);
-    const double nx3sq = -(x3 * x3) * kLog2e * kExp2Scale;  // the exponential as 2^(u / 256)
-    E = nx3sq * a[0];
-    F = nx3sq * b[0];
-    A2 = a[1];
-    B2 = b[1];
+    x1 = x.next(0) * kInv2Pi;
+    x2 = x.next(1) * kInv2Pi;
+    const double x3 = x.next(2);
+    nx3sq = -(x3 * x3) * kLog2e;
     x4 = x.next(3);
   }
-  __device__ __forceinline__ double value(const double* t) const {
-    double ph = C;
+  __host__ __device__ __forceinline__ double value(const double* t) const {
+    const double y1 = fmaT(A[0], t[0], B[0]);
+    const double y2 = fmaT(A[1], t[1], B[1]);
+    double ph = fmaT(x1, y1, x2 * y2);
 #pragma unroll
-    for (int k = 0; k < N; ++k) ph = fmaT(P[k], t[k], ph);
-    const double e = fmaT(E, t[0], F) * fmaT(A2, t[1], B2);
-    return __builtin_fma(cos_turns(ph), exp2_units(e), x4);
+    for (int k = 2; k < N; ++k) ph += fmaT(A[k], t[k], B[k]);
+    return __builtin_fma(cos_turns(ph), exp2_fp64(nx3sq * y1 * y2), x4);
   }
 };
 

@@ -29,3 +29,11 @@ def test_sin_of_small_phases_keeps_its_relative_accuracy(tmp_path):
     e1, e3, bad, out = _run("small_phase", tmp_path)
     assert float(e1) < 1.0 and float(e3) < 1.0, (e1, e3)
     assert int(bad) == 0 and int(out) == 0
+
+
+def test_cosexp_exponent_and_phase_over_their_ranges(tmp_path):
+    """The exponent within the roundings of its factors where they are near 0 (boxes
+    [-1, 0] and [-3, -1/2], x3 up to 1000), the phase within those of its terms, and
+    2^t of an exponent that overflows as exp gives it."""
+    e, c, bad = _run("cosexp_ranges", tmp_path)
+    assert float(e) < 1.0 and float(c) < 1.0 and int(bad) == 0, (e, c, bad)

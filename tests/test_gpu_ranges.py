@@ -38,3 +38,19 @@ def test_small_phases(w, N):
         _check(spec, f, s, f"w={w} N={N} {mode}")
     (f, s), = zmc.scan_batch([spec])
     _check(spec, f, s, f"w={w} N={N} batch")
+
+
+# exponents -x3^2 y1 y2 of samples near the edge of [-1, 0]^2, where only small
+# coordinates count
+@pytest.mark.parametrize("x3", [1.0, 30.0, 1000.0])
+@pytest.mark.parametrize("N", [2, 5, 12])
+def test_cosexp_exponents_on_negative_boxes(N, x3):
+    import torch
+    from paper_1910_01965_amd import zmc
+    axes = [np.array([0.0, 0.3]), np.array([0.1, 0.2]), x3 * np.array([0.5, 1.0]), np.array([0.0])]
+    spec = wl.ScanSpec("cosexp", axes, -np.ones(N), np.zeros(N), 4099, 9, "fp64")
+    for mode in ("point_major", "sample_major"):
+        print("cosexp exponents", N, x3, mode, flush=True)
+        f, s = zmc.scan(spec, mode=mode)
+        torch.cuda.synchronize()
+        _check(spec, f, s, f"x3={x3} N={N} {mode}")
