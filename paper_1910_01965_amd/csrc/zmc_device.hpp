@@ -1107,6 +1107,14 @@ __device__ __forceinline__ double wave_sum(double x) {
   return x;
 }
 
+// The first lane's value (wave-uniform).
+__device__ __forceinline__ double first_lane(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 // Samples in split sp (groups [sp*gps, min((sp+1)*gps, n_groups)), the last
 // group of the scan possibly short).
 __host__ __device__ __forceinline__ uint64_t split_samples(uint64_t n, uint64_t n_groups,

@@ -61,7 +61,7 @@ std::string program_text(const std::string& user, int precision, int N, int M) {
     if (*big && N > zmc::kAnyMaxDims) continue;
     s += std::string("extern \"C\" __global__ __launch_bounds__(") + (*big ? "1024" : "256") +
          ") void zmc_user_sample_major" + big + "(zmc::ScanParams p) {\n";
-    s += "  __shared__ double lds[48];\n  zmc::sample_major_body<" + fam + ">(p, lds);\n}\n";
+    s += "  __shared__ double lds[zmc::kSmLds];\n  zmc::sample_major_body<" + fam + ">(p, lds);\n}\n";
   }
   s += "extern \"C\" __global__ __launch_bounds__(256) void zmc_user_values(zmc::ScanParams p, "
        "uint64_t g, uint64_t s0, int64_t count, double* out) {\n";
@@ -69,7 +69,7 @@ std::string program_text(const std::string& user, int precision, int N, int M) {
   s += "extern \"C\" __global__ __launch_bounds__(256) void zmc_user_batch("
        "const zmc::ScanParams* __restrict__ scans, const zmc::Tile* __restrict__ tiles, "
        "uint32_t begin, uint32_t end, uint32_t* counter) {\n";
-  s += "  __shared__ uint32_t next;\n  __shared__ double lds[48];\n";
+  s += "  __shared__ uint32_t next;\n  __shared__ double lds[zmc::kSmLds];\n";
   s += "  zmc::batch_body<" + fam + ">(scans, tiles, begin, end, counter, &next, lds);\n}\n";
   return s;
 }

@@ -133,13 +133,17 @@ __device__ __forceinline__ double strided_groups(const Fam& fam, const Gen& gen,
 // g) over sample piece sp by the `waves` waves of the block from wave w0 on: lane
 // t of them takes groups j0 + t, j0 + t + T, ... (T: the lanes of the whole block;
 // fewer waves than the block's are used for pieces of at most as many groups as
-// they have lanes).  Then the lanes are merged: the mean of all
-// samples from the lanes' sums, then M2 = sum_lanes (M2_lane + n_lane (mean_lane -
-// mean)^2).  Two sums of one double over the block replace a tree of pairwise
+// they have lanes).  Then the lanes are merged: the mean of all samples as the first
+// lane's plus the sum of the lanes' differences from it, each weighted by its share
+// of the samples (a sum of n_lane mean_lane would overflow for means above the
+// largest double / n), the waves' likewise, and M2 = sum_lanes (M2_lane + n_lane
+// (mean_lane - mean)^2).  Sums over the block replace a tree of pairwise
 // merges of three doubles, each with a division (about 1.3 us of a block's
 // time; a 10^4-point FP64 scan of 1024 samples, N = 4: 86 -> 55 us).
 // Every thread of the block must call it, those with no point to work on with
-// `active` false (it synchronises unless `waves` is 1); `lds` holds 3 x 16 doubles.
+// `active` false (it synchronises unless `waves` is 1); `lds` holds kSmLds doubles.
+constexpr int kSmLds = 4 * 16;  // four values of each of a block's waves
+
 template <class Fam, typename T, int N>
 __device__ __forceinline__ void sm_work(const ScanParams& p, uint64_t g, uint64_t sp, double* lds,
                                         unsigned w0, unsigned waves, bool active) {
@@ -187,22 +191,30 @@ __device__ __forceinline__ void sm_work(const ScanParams& p, uint64_t g, uint64_
   }
   const Moments m = to_moments(acc, count);
   const double n = (double)split_samples(p.n, p.n_groups, p.gps, sp);
-  double mean = wave_sum(m.n * m.mean);
+  const double wt = m.n / n;
+  double ref = first_lane(m.mean);
+  double s = wave_sum(m.n > 0.0 ? wt * (m.mean - ref) : 0.0);
   const unsigned w = threadIdx.x >> 6;
   if (waves > 1) {
-    if ((threadIdx.x & 63u) == 0) lds[w] = mean;
+    const double wave_wt = wave_sum(wt);
+    if ((threadIdx.x & 63u) == 0) {
+      lds[w] = s;
+      lds[16 + w] = ref;
+      lds[32 + w] = wave_wt;
+    }
     __syncthreads();
-    mean = lds[w0];
-    for (unsigned i = 1; i < waves; ++i) mean += lds[w0 + i];
+    s = lds[w0];
+    ref = lds[16 + w0];
+    for (unsigned i = 1; i < waves; ++i) s += lds[w0 + i] + lds[32 + w0 + i] * (lds[16 + w0 + i] - ref);
   }
-  mean /= n;
+  const double mean = ref + s;
   const double d = m.mean - mean;
   double m2 = wave_sum(m.n > 0.0 ? m.m2 + m.n * d * d : 0.0);
   if (waves > 1) {
-    if ((threadIdx.x & 63u) == 0) lds[16 + w] = m2;
+    if ((threadIdx.x & 63u) == 0) lds[48 + w] = m2;
     __syncthreads();
-    m2 = lds[16 + w0];
-    for (unsigned i = 1; i < waves; ++i) m2 += lds[16 + w0 + i];
+    m2 = lds[48 + w0];
+    for (unsigned i = 1; i < waves; ++i) m2 += lds[48 + w0 + i];
   }
   if (lane == 0 && active) {
     if (p.splits == 1) {

@@ -35,7 +35,7 @@ constexpr int kSmMinWaves = sizeof(T) == 4 ? 4 : N <= 5 ? 3 : 2;
 template <class Fam, typename T, int N, int MaxThreads>
 __global__ __launch_bounds__(MaxThreads, (MaxThreads > 256 ? 1 : kSmMinWaves<T, N>))
 void k_sample_major(ScanParams p) {
-  __shared__ double lds[48];
+  __shared__ double lds[kSmLds];
   sample_major_body<Fam, T, N>(p, lds);
 }
 
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(256, (kMinWaves<T, N>)) void k_batch(const ScanPara
                                                const Tile* __restrict__ tiles, uint32_t begin,
                                                uint32_t end, uint32_t* counter) {
   __shared__ uint32_t next;
-  __shared__ double lds[48];
+  __shared__ double lds[kSmLds];
   batch_body<Fam, T, N>(scans, tiles, begin, end, counter, &next, lds);
 }
 
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_batch_any(const
                                                    const Tile* __restrict__ tiles, uint32_t begin,
                                                    uint32_t end, uint32_t* counter) {
   __shared__ uint32_t next;
-  __shared__ double lds[48];
+  __shared__ double lds[kSmLds];
   if constexpr (sizeof(T) == 8) exp2_table_load();
   uint32_t popped = 0;  // as in batch_body
   bool have = false;

@@ -54,3 +54,18 @@ def test_cosexp_exponents_on_negative_boxes(N, x3):
         f, s = zmc.scan(spec, mode=mode)
         torch.cuda.synchronize()
         _check(spec, f, s, f"x3={x3} N={N} {mode}")
+
+
+# every sample is x4 to the last bit: a sum of n x4 overflows, the mean does not
+@pytest.mark.parametrize("samples", [2, 200, 500, 1031, 4100, 70001])
+def test_means_near_the_largest_double(samples):
+    import torch
+    from paper_1910_01965_amd import zmc
+    axes = [np.array([0.2]), np.array([0.3]), np.array([0.4]), np.array([1e306, -1.7e308])]
+    spec = wl.ScanSpec("cosexp", axes, np.zeros(3), np.ones(3), samples, 11, "fp64")
+    runs = [zmc.scan(spec, mode=m) for m in ("sample_major", "point_major")]
+    runs += [zmc.scan(spec, mode="sample_major", block=1024), zmc.scan_batch([spec])[0]]
+    torch.cuda.synchronize()
+    for i, (f, s) in enumerate(runs):
+        print("large means", samples, i, flush=True)
+        assert f.cpu().tolist() == [1e306, -1.7e308] and s.cpu().tolist() == [0.0, 0.0]
