@@ -28,11 +28,14 @@ namespace zmc {
 // (about 0.3 ms in FP64).
 constexpr uint64_t kShortTileBlocks = 1024;
 
-// Tiles that a scan's grid is cut into, its sample range included, and the
-// shortest pieces for that: 8192 tiles are about five rounds of the device's
-// resident blocks, and in 128 groups the set-up is 3 %.
-// The partials of such a scan stay below 16 B x 256 x 2 x 8192 = 64 MiB.
-constexpr uint64_t kFineTiles = 8192;
+// The finer cut of FP64 point-major scans: the partials that it may add up to, and
+// its shortest pieces.  8 MiB are 2048 tiles of any grid (256 points x 16 B x 2048),
+// two for each block that the device holds, so that the few scans of a small mix
+// fill it; a scan that has more tiles already, and a large batch, gain nothing from
+// the cut, and 1000 scans hold 8 GiB for it at most.  24 scans of up to 10^5
+// points x 32768 samples take 8.9 ms, with 4 MiB 11.3, with 2 MiB 13.1, with 32 MiB
+// 8.5, uncut 10.7.  In 128 groups the set-up is 3 %.
+constexpr uint64_t kFinePartialBytes = (uint64_t)8 << 20;
 constexpr uint64_t kFineGroups = 128;
 
 // The tiled decomposition of one scan (batches and the server): a function of
@@ -40,8 +43,7 @@ constexpr uint64_t kFineGroups = 128;
 // what else runs with it.  Point-major tiles hold 256 consecutive points and
 // `pm_groups` groups of four samples per lane; grids below `pm_min_points`
 // get sample-major tiles of `sm_groups` groups (all lanes together) and a few
-// points.  The partials of one scan are kept below 2 GiB by lengthening its pieces;
-// FP64 pieces are cut finer only while the partials stay within max_partial_bytes.
+// points.  The partials of one scan are kept below 2 GiB by lengthening its pieces.
 zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_override,
                       int64_t sm_groups_override, int64_t pm_min_override, Plan* pl,
                       uint64_t* tiles, uint64_t max_partial_bytes) {
@@ -69,15 +71,13 @@ zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_over
   splits = (groups + gps - 1) / gps;
   // A lane walks its piece's samples one after another, so a tile of the table's
   // length (up to 8192 groups) lasts milliseconds, which the scans of a small mix
-  // wait for while the device drains: FP64 grids of fewer than kFineTiles blocks
-  // of points get more, shorter pieces.  FP32 keeps the table's pieces: another cut
+  // wait for while the device drains: FP64 grids get more, shorter pieces, as many as
+  // kFinePartialBytes hold.  FP32 keeps the table's pieces: another cut
   // moves its results by roundings of the lanes' sums (up to 8e-9 of sigma).
   const uint64_t point_blocks = (G + kTileBlock - 1) / kTileBlock;
-  if (pl->mode == ZMC_MODE_POINT_MAJOR && pm_groups_override <= 0 && d->precision == ZMC_FP64 &&
-      point_blocks < kFineTiles) {
-    const uint64_t fine = std::min<uint64_t>((kFineTiles + point_blocks - 1) / point_blocks,
-                                             groups / kFineGroups);
-    if (fine > splits && 16 * fine * G <= max_partial_bytes) {
+  if (pl->mode == ZMC_MODE_POINT_MAJOR && pm_groups_override <= 0 && d->precision == ZMC_FP64) {
+    const uint64_t fine = std::min<uint64_t>(std::min(kFinePartialBytes, max_partial_bytes) / 16 / G, groups / kFineGroups);
+    if (fine > splits) {
       gps = (groups + fine - 1) / fine;
       splits = (groups + gps - 1) / gps;
     }
