@@ -46,7 +46,7 @@ constexpr uint64_t kFineGroups = 128;
 // points.  The partials of one scan are kept below 2 GiB by lengthening its pieces.
 zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_override,
                       int64_t sm_groups_override, int64_t pm_min_override, Plan* pl,
-                      uint64_t* tiles, uint64_t max_partial_bytes) {
+                      uint64_t* tiles) {
   const TuneEntry t = tune_lookup(d->family, d->precision, d->N);
   const int64_t pm_groups = pm_groups_override > 0 ? pm_groups_override : t.pm_groups;
   const int64_t sm_groups = sm_groups_override > 0 ? sm_groups_override : t.sm_groups;
@@ -69,6 +69,7 @@ zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_over
   if (splits > 0x7FFFFFFFull) return fail(ZMC_E_UNSUPPORTED, "too many sample pieces");
   uint64_t gps = (groups + splits - 1) / splits;
   splits = (groups + gps - 1) / gps;
+  pl->table_bytes = splits > 1 ? 16 * splits * G : 0;
   // A lane walks its piece's samples one after another, so a tile of the table's
   // length (up to 8192 groups) lasts milliseconds, which the scans of a small mix
   // wait for while the device drains: FP64 grids get more, shorter pieces, as many as
@@ -76,7 +77,7 @@ zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_over
   // moves its results by roundings of the lanes' sums (up to 8e-9 of sigma).
   const uint64_t point_blocks = (G + kTileBlock - 1) / kTileBlock;
   if (pl->mode == ZMC_MODE_POINT_MAJOR && pm_groups_override <= 0 && d->precision == ZMC_FP64) {
-    const uint64_t fine = std::min<uint64_t>(std::min(kFinePartialBytes, max_partial_bytes) / 16 / G, groups / kFineGroups);
+    const uint64_t fine = std::min<uint64_t>(kFinePartialBytes / 16 / G, groups / kFineGroups);
     if (fine > splits) {
       gps = (groups + fine - 1) / fine;
       splits = (groups + gps - 1) / gps;

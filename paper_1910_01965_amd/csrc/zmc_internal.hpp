@@ -21,6 +21,7 @@ struct Plan {
   uint64_t point_blocks;
   uint64_t workspace_bytes;
   uint32_t sm_points;   // points of a sample-major tile (plan_tiles)
+  uint64_t table_bytes; // partials that the tuned table's own pieces need (plan_tiles)
 };
 
 hipError_t launch_scan(const ScanParams& p, const Plan& plan, int precision, hipStream_t stream,
@@ -55,7 +56,7 @@ constexpr int kTileBlock = 256;
 constexpr uint64_t kMaxPartialBytesPerScan = (uint64_t)2 << 30;
 zmc_status plan_tiles(const zmc_scan_desc* d, uint64_t G, int64_t pm_groups_override,
                       int64_t sm_groups_override, int64_t pm_min_override, Plan* pl,
-                      uint64_t* tiles, uint64_t max_partial_bytes = ~(uint64_t)0);
+                      uint64_t* tiles);
 const char* tune_source();
 hipError_t batch_occupancy(int precision, int family, int N, int* blocks_per_cu);
 hipError_t launch_batch_variant(int precision, int family, int N, const ScanParams* scans,

@@ -51,7 +51,8 @@ struct Request {
   uint64_t total_tiles = 0, next_tile = 0;
   uint64_t tile_samples = 1;  // samples per tile, averaged over the request's tiles
   uint64_t staged_doubles = 0;
-  uint64_t footprint = 0;
+  uint64_t footprint = 0;     // device bytes
+  uint64_t charge = 0;        // of them, what counts against the budget
   double work = 0.0;          // estimated device work G * samples * N (admission order)
   zmc::UserKernels user;      // family ZMC_USER: kernels built for this shape
   unsigned own_blocks = 0;    // resident blocks of the request's own batch kernel
@@ -387,7 +388,7 @@ void retire(zmc_server* s, Slice& sl) {
   for (const ReqPtr& r : sl.finishing) {
     if (r->dmem) (void)hipFreeAsync(r->dmem, s->streams[r->alloc_stream]);
     r->dmem = nullptr;
-    s->bytes_in_use -= r->footprint;
+    s->bytes_in_use -= r->charge;
     s->free_slots.push_back(r->slot);
     finish(s, r, ZMC_OK);
   }
@@ -488,7 +489,7 @@ void run(zmc_server* s) {
     while (!s->pending.empty() && !s->free_slots.empty()) {
       const size_t j = next_pending(s);
       ReqPtr r = s->pending[j];
-      if (r->footprint > s->opts.hbm_budget_bytes) {
+      if (r->charge > s->opts.hbm_budget_bytes) {
         s->pending.erase(s->pending.begin() + (std::ptrdiff_t)j);
         bool cancelled;
         {
@@ -498,7 +499,7 @@ void run(zmc_server* s) {
         finish(s, r, cancelled ? ZMC_E_CANCELLED : ZMC_E_NOMEM);
         continue;
       }
-      if (s->bytes_in_use + r->footprint > s->opts.hbm_budget_bytes) break;
+      if (s->bytes_in_use + r->charge > s->opts.hbm_budget_bytes) break;
       s->pending.erase(s->pending.begin() + (std::ptrdiff_t)j);
       {
         // from here the request is admitted: zmc_server_cancel answers BUSY
@@ -532,7 +533,7 @@ void run(zmc_server* s) {
         broken = true;
         break;
       }
-      s->bytes_in_use += r->footprint;
+      s->bytes_in_use += r->charge;
       zmc::log(2, "server: request %llu admitted (slot %d, %llu B, %llu tiles)",
                (unsigned long long)r->ticket, r->slot, (unsigned long long)r->footprint,
                (unsigned long long)r->total_tiles);
@@ -715,15 +716,15 @@ zmc_status zmc_server_submit(zmc_server* s, const zmc_scan_desc* desc, const dou
   r->d_f = d_f;
   r->d_sigma = d_sigma;
   r->G = G;
-  // a finer cut than the tuned table's must not make a request too large for the
-  // whole budget
-  const uint64_t staged = align_up(8 * r->staged_doubles);
-  st = zmc::plan_tiles(&r->desc, G, 0, 0, 0, &r->plan, &r->total_tiles,
-                       s->opts.hbm_budget_bytes > staged ? s->opts.hbm_budget_bytes - staged : 0);
+  st = zmc::plan_tiles(&r->desc, G, 0, 0, 0, &r->plan, &r->total_tiles);
   if (st != ZMC_OK) return st;
   r->tile_samples = (uint64_t)std::max(
       1.0, (double)G * (double)desc->samples / (double)std::max<uint64_t>(1, r->total_tiles));
-  r->footprint = align_up(8 * r->staged_doubles) + r->plan.workspace_bytes;
+  const uint64_t staged = align_up(8 * r->staged_doubles);
+  r->footprint = staged + r->plan.workspace_bytes;
+  // the finer cut must not make a request too large for the whole budget: one that
+  // fits with the table's pieces is admitted as if it had them
+  r->charge = r->footprint <= s->opts.hbm_budget_bytes ? r->footprint : staged + r->plan.table_bytes;
   r->work = (double)G * (double)r->desc.samples * (double)r->desc.N;
   {
     std::lock_guard<std::mutex> lk(s->mu);
