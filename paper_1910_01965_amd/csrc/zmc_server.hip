@@ -265,11 +265,22 @@ hipError_t launch_slice(zmc_server* s, int si, Slice* out) {
   // tile table: FP32 tiles and FP64 tiles of the any-family kernels, then one
   // group per variant that runs in a kernel of its own: a user integrand
   // (integrand, precision, N, M) or a compiled-in family with
-  // N > kAnyMaxDims (family, precision, N)
+  // N > kAnyMaxDims (family, precision, N).  Within the any-family kernels the tiles
+  // of one (family, N) follow each other, so that blocks which share an instruction
+  // cache (two CUs, 64 KB; one variant's loops are 10 to 20 KB) run the same code:
+  // 11963 requests at 200 a second are served in 140.5 s, and took 145.9 in the
+  // order of admission (145.3 before the kernels' phases, whose loops are longer).
+  std::vector<const std::pair<ReqPtr, uint64_t>*> by_variant;
+  for (const auto& tk : take) by_variant.push_back(&tk);
+  std::stable_sort(by_variant.begin(), by_variant.end(), [](const auto* a, const auto* b) {
+    const zmc_scan_desc &x = a->first->desc, &y = b->first->desc;
+    return x.family != y.family ? x.family < y.family : x.N < y.N;
+  });
   uint32_t n32 = 0, n = 0;
   for (int pass = 0; pass < 2; ++pass) {
     const int prec = pass == 0 ? ZMC_FP32_MERGE64 : ZMC_FP64;
-    for (auto& tk : take) {
+    for (const auto* at : by_variant) {
+      const auto& tk = *at;
       Request& r = *tk.first;
       if (r.desc.precision != prec || own_kernel(r)) continue;
       for (uint64_t t = 0; t < tk.second; ++t) ht[n++] = tile_of(r, r.next_tile + t);
