@@ -9,18 +9,32 @@
 
 namespace zmc {
 
-// Waves per SIMD asked of the point-major and batch kernels: enough for the
-// issue phases to pair (two waves pair 60 % as often as four), and as many as
-// fit without spilling in the loop.  FP32 at 5 against the compiler's own
-// choice: Gaussian N = 8 0.98 vs 1.05 ms, SIN_SUM N = 12 1.31 vs 1.47 ms
-// (5e5 points x 1024 samples); at 6 the N = 12 Gaussian spills (2.03 vs
-// 1.45 ms).  FP64 at 4 up to N = 8 (Gaussian N = 8 1.48 vs 1.63 ms) and 3
-// beyond (Gaussian N = 12 2.07 vs 2.30 ms); at 5 it spills from N = 7.
-template <typename T, int N>
-constexpr int kMinWaves = sizeof(T) == 4 ? 5 : N <= kAnyMaxDims ? 4 : 3;
+// Waves per SIMD asked of the kernels: enough for the issue phases to pair (two
+// waves pair 60 % as often as four), unless what they then spill in the set-up and
+// around the loops costs more.  Chosen from timings of each kernel at one and two
+// waves less, N = 3..16, SIN_SUM, GAUSS and COSEXP.  GAUSS, whose kernels hold a
+// general and a reduced form, spills first.
+template <class Fam> constexpr bool kTwoForms = HasUnitForm<Fam>::value;
+
+// Point-major.  FP32 at 5 against 4: SIN_SUM N = 16 4 % faster, COSEXP 3 %, Gaussian
+// N = 8 0.98 vs 1.05 ms (5e5 points x 1024 samples), but Gaussian N = 13 467 vs 418 us,
+// N = 16 1140 vs 483 us (10^5 points x 1024 samples; 608 at the compiler's own choice
+// of unphased kernels).  FP64 at 4 up to N = 8 (Gaussian N = 8 1.48 vs 1.63 ms) and 3
+// beyond (Gaussian N = 12 2.07 vs 2.30 ms).
+template <class Fam, typename T, int N>
+constexpr int kMinWaves = sizeof(T) == 4 ? (kTwoForms<Fam> && N > kAnyMaxDims ? 4 : 5) : N <= kAnyMaxDims ? 4 : 3;
+
+// Batch kernels hold the point-major and the sample-major loops.  FP32 at 5, 4 and 3:
+// 12 scans of 600 to 1000 points, N = 8, 119 : 100 : 100 for the Gaussian and 113 : 100 :
+// 103 for SIN_SUM, 4 scans of 40000 points 128 : 100 : 113 and 104 : 100 : 118; N = 16
+// Gaussian 206 : 100 : 77.  FP64 at 4 against 3: COSEXP N = 8 121 : 100, N = 7 97 : 100; at 3
+// against 2: N = 16 118 to 137 : 100 in small scans, 85 to 93 : 100 in large ones.
+template <class Fam, typename T, int N>
+constexpr int kBatchWaves = sizeof(T) == 4 ? (N <= 6 ? 5 : kTwoForms<Fam> && N == 16 ? 3 : 4)
+                                           : (N < kAnyMaxDims ? 4 : N < 16 ? 3 : 2);
 
 template <class Fam, typename T, int N>
-__global__ __launch_bounds__(256, (kMinWaves<T, N>)) void k_point_major(ScanParams p) {
+__global__ __launch_bounds__(256, (kMinWaves<Fam, T, N>)) void k_point_major(ScanParams p) {
   point_major_body<Fam, T, N>(p);
 }
 
@@ -28,12 +42,19 @@ __global__ __launch_bounds__(256, (kMinWaves<T, N>)) void k_point_major(ScanPara
 // up to 1024 for N <= kAnyMaxDims (explicit plans), whose bound of 128 VGPRs a
 // lane makes the FP64 kernels spill.  One or two waves per SIMD less than for
 // the point-major kernels: the lane's word block and the point's Philox constants
-// take some 20 VGPRs more.
-template <typename T, int N>
-constexpr int kSmMinWaves = sizeof(T) == 4 ? 4 : N <= 5 ? 3 : 2;
+// take some 20 VGPRs more, and what short scans spill in the set-up is most of them:
+// Gaussian FP32, 1000 points x 1000 samples, at 4, 3 and 2 waves N = 8 20.8, 17.7 and
+// 17.8 us, N = 12 32.6, 23.6 and 20.4, N = 16 47.4, 47.2 and 25.3 (unphased 18.1, 21.5, 27.1);
+// 1500 points x 32768 samples N = 10 105 : 100 : 107.  Others FP32 at 4 and 3: N = 16
+// 116 to 123 : 100 in such short scans, 97 to 101 : 100 in long ones.  FP64 Gaussian at 2 and 1:
+// N = 16 52 and 39.5 us (36.9 unphased), long scans 83 : 100.
+template <class Fam, typename T, int N>
+constexpr int kSmMinWaves = sizeof(T) == 8 ? (N <= 5 ? 3 : kTwoForms<Fam> && N >= 15 ? 1 : 2)
+                            : kTwoForms<Fam> ? (N <= 6 ? 4 : N <= 10 ? 3 : 2)
+                                             : (N <= 12 ? 4 : 3);
 
 template <class Fam, typename T, int N, int MaxThreads>
-__global__ __launch_bounds__(MaxThreads, (MaxThreads > 256 ? 1 : kSmMinWaves<T, N>))
+__global__ __launch_bounds__(MaxThreads, (MaxThreads > 256 ? 1 : kSmMinWaves<Fam, T, N>))
 void k_sample_major(ScanParams p) {
   __shared__ double lds[kSmLds];
   sample_major_body<Fam, T, N>(p, lds);
@@ -44,7 +65,7 @@ void k_sample_major(ScanParams p) {
 // counter (tiles are sorted longest first) and exit once the table is
 // exhausted; every block reaches that exit.
 template <class Fam, typename T, int N>
-__global__ __launch_bounds__(256, (kMinWaves<T, N>)) void k_batch(const ScanParams* __restrict__ scans,
+__global__ __launch_bounds__(256, (kBatchWaves<Fam, T, N>)) void k_batch(const ScanParams* __restrict__ scans,
                                                const Tile* __restrict__ tiles, uint32_t begin,
                                                uint32_t end, uint32_t* counter) {
   __shared__ uint32_t next;
@@ -89,9 +110,11 @@ __device__ __forceinline__ void run_tile_any(const ScanParams& p, const Tile& tl
 }
 
 // Batched scans, one kernel for every family (N <= kAnyMaxDims) of one
-// working precision: the blocks pop tiles of all scans from one queue.  FP32
-// fits four waves per SIMD; FP64 spills beyond two (at four waves a served
-// FP64 mix took 3.8 ms instead of 3.1).
+// working precision: the blocks pop tiles of all scans from one queue.  FP32 at
+// four waves per SIMD spills 49 VGPRs, none of them inside a loop over groups (a build
+// that spilled 5 served 7.07e11 samples/s of the mix that this one serves at 7.05e11;
+// at five waves 2 % less); FP64 spills in the loops beyond two (at four waves a
+// served FP64 mix took 3.8 ms instead of 3.1).
 template <typename T>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_batch_any(const ScanParams* __restrict__ scans,
                                                    const Tile* __restrict__ tiles, uint32_t begin,
