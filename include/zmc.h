@@ -176,15 +176,17 @@ zmc_status zmc_scan(const zmc_scan_desc* desc, double* f, double* sigma);
  * stream capture that gives ZMC_E_INVALID (a replay cannot re-read host
  * memory), and with both pointers NULL too.
  * Split partials, when the plan needs them (16 B per point and sample
- * piece), come from a per-device cache of at most four buffers of
- * power-of-two sizes from 1 MiB to 256 MB, held by the library until the
- * process ends and reused
+ * piece; zmc_plan tells: plans with several pieces, among them those of many short
+ * FP64 scans of 64 to 65535 points on 256 compute units), come from a per-device
+ * cache of at most 16 buffers of 1 to 8 MiB and four of 16 to 256 MiB, in
+ * power-of-two sizes, held by the library until the process ends and reused
  * without a host wait (a buffer still in use by another call's kernels is
  * ordered after them on the device); larger partials, and every call made
  * under stream capture, live in stream-ordered device memory released on
  * the same stream.  Returns after enqueueing.
  * The call may be recorded by stream capture into a caller's HIP graph
- * (kernels plus, for split plans, graph memory nodes; no memset nodes); each
+ * (kernels plus, for split plans, graph memory nodes; no memset nodes:
+ * zmc_scan_device_noalloc records kernels only); each
  * replay recomputes the same results, provided the device has been used
  * once (the compute-unit count is cached) before the capture begins. */
 zmc_status zmc_scan_device(const zmc_scan_desc* desc, const double* d_axis_vals,

@@ -354,7 +354,9 @@ namespace {
 // uses it and that kernel's stream.
 // A call takes, among the buffers large enough, one whose event has completed;
 // else one last used on the same stream; else a new one while the device holds
-// fewer than kMaxCachedBuffers; else any.  A buffer whose event is pending is
+// fewer than its size's limit (16 buffers of up to 8 MiB: mid-sized FP64 scans,
+// whose partials take up to 5.3 MB, then need not wait for each other on as many
+// streams; 4 larger ones); else any.  A buffer whose event is pending is
 // ordered after that event on the device (hipStreamWaitEvent), never on the
 // host.  Larger workspaces, whose scans take far longer than that host wait,
 // and every call under capture (where the graph must own its memory as graph
@@ -370,12 +372,13 @@ struct Workspace {
 
 struct DeviceWorkspaces {
   std::vector<Workspace> idle;  // buffers not held by a call
-  int count = 0;                // idle + held
+  int count[2] = {0, 0};        // idle + held: larger ones, small ones
 };
 
 constexpr int kMaxWsDevices = 64;
 constexpr size_t kMaxCachedWorkspace = (size_t)256 << 20;  // bytes of one cached buffer
-constexpr int kMaxCachedBuffers = 4;                        // buffers per device, held ones included
+constexpr size_t kSmallWorkspace = (size_t)8 << 20;
+constexpr int kMaxCachedBuffers[2] = {4, 16};  // per device, held ones included: larger ones, small ones
 std::mutex g_ws_mu;
 DeviceWorkspaces g_ws[kMaxWsDevices];
 
@@ -384,6 +387,7 @@ DeviceWorkspaces g_ws[kMaxWsDevices];
 hipError_t ws_acquire(int dev, size_t bytes, hipStream_t s, Workspace* out) {
   Workspace drop;  // a too-small idle buffer freed to keep the count bounded
   bool reuse = false;
+  const int small = bytes <= kSmallWorkspace ? 1 : 0;
   {
     std::lock_guard<std::mutex> lk(g_ws_mu);
     DeviceWorkspaces& D = g_ws[dev];
@@ -396,21 +400,22 @@ hipError_t ws_acquire(int dev, size_t bytes, hipStream_t s, Workspace* out) {
     };
     int i = pick([](const Workspace& w) { return !w.used || hipEventQuery(w.done) == hipSuccess; });
     if (i < 0) i = pick([&](const Workspace& w) { return w.last == s; });
-    if (i < 0 && D.count >= kMaxCachedBuffers) i = pick([](const Workspace&) { return true; });
+    const bool full = D.count[small] >= kMaxCachedBuffers[small];
+    if (i < 0 && full) i = pick([](const Workspace&) { return true; });
     if (i >= 0) {
       *out = L[i];
       L.erase(L.begin() + i);
       reuse = true;
     } else {
-      if (D.count >= kMaxCachedBuffers && !L.empty()) {  // none fits: retire the smallest
-        int j = 0;
-        for (int k = 1; k < (int)L.size(); ++k)
-          if (L[k].bytes < L[j].bytes) j = k;
+      int j = -1;  // none fits: retire the smallest of its kind
+      for (int k = 0; full && k < (int)L.size(); ++k)
+        if ((L[k].bytes <= kSmallWorkspace ? 1 : 0) == small && (j < 0 || L[k].bytes < L[j].bytes)) j = k;
+      if (j >= 0) {
         drop = L[j];
         L.erase(L.begin() + j);
-        --D.count;
+        --D.count[small];
       }
-      ++D.count;
+      ++D.count[small];
     }
   }
   if (reuse) {
@@ -437,7 +442,7 @@ hipError_t ws_acquire(int dev, size_t bytes, hipStream_t s, Workspace* out) {
   if (e != hipSuccess) {
     if (w.ptr) (void)hipFree(w.ptr);
     std::lock_guard<std::mutex> lk(g_ws_mu);
-    --g_ws[dev].count;
+    --g_ws[dev].count[small];
     return e;
   }
   *out = w;
