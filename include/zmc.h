@@ -202,7 +202,8 @@ zmc_status zmc_scan_device(const zmc_scan_desc* desc, const double* d_axis_vals,
  * default 8); outputs in pinned memory
  * (hipHostMalloc) take the copies directly.  Device memory: the lists plus
  * 2 x 16 B x chunk_points plus the chunk's split partials.  A scan of one chunk
- * whose lists, f and sigma fit 4 MiB runs through a stream and pinned staging
+ * whose lists, f and sigma fit 4 MiB, and with its partials 8 MiB of device
+ * memory, runs through a stream and pinned staging
  * that the library keeps (at most four of each per device) and the workspace
  * cache of zmc_scan_device.  Synchronous.
  * f and sigma must be host memory (ZMC_E_INVALID for device pointers). */

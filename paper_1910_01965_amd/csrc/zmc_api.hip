@@ -827,7 +827,9 @@ void lane_release(int dev, const HostLane& L) {
 }
 
 // One chunk of a host-memory scan whose lists, f and sigma fit a lane's staging.
-// Device memory (lists, f and sigma, partials) comes from the workspace cache.
+// Device memory (lists, f and sigma, partials) comes from the workspace cache; scans
+// that need more than its small buffers take the chunk pipeline, which frees its
+// memory (a scan that lasts milliseconds gains nothing here).
 hipError_t scan_small_range(int dev, const zmc_scan_desc* desc, const zmc::UserKernels& uk,
                             const zmc::Plan& pl, uint64_t g_begin, uint64_t n, uint64_t n_axis,
                             double* f, double* sigma) {
@@ -864,7 +866,10 @@ hipError_t scan_small_range(int dev, const zmc_scan_desc* desc, const zmc::UserK
     memcpy(f, L.pinned + off_out, 8 * n);
     memcpy(sigma, L.pinned + off_out + 8 * n, 8 * n);
   }
-  lane_release(dev, L);
+  if (e == hipSuccess)
+    lane_release(dev, L);
+  else
+    lane_free(L);  // its stream may hold the error
   return e;
 }
 
@@ -935,8 +940,8 @@ zmc_status zmc_scan_range(const zmc_scan_desc* desc, uint64_t g_begin, uint64_t 
 
   int dev = 0;
   ZMC_HIP(hipGetDevice(&dev));
-  if (R == C && off_out + 16 * C + 256 <= kLaneBytes && total <= kMaxCachedWorkspace && dev >= 0 &&
-      dev < kMaxWsDevices) {
+  if (R == C && off_out + 16 * C + 256 <= kLaneBytes && off_ws + cp.workspace_bytes <= kSmallWorkspace &&
+      dev >= 0 && dev < kMaxWsDevices) {
     const hipError_t es = scan_small_range(dev, desc, uk, cp, g_begin, R, n_axis, f, sigma);
     if (es != hipSuccess)
       return fail(es == hipErrorOutOfMemory ? ZMC_E_NOMEM : ZMC_E_DEVICE, "scan failed: %s",

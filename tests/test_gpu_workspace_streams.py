@@ -49,3 +49,16 @@ def test_mid_sized_scans_on_eight_streams_have_their_own_workspaces():
         "torch.cuda.synchronize()\n"
         "assert all(torch.equal(f, out[0][0]) and torch.equal(s, out[0][1]) for f, s in out)\n")
     assert len(new) == 8, new
+
+
+def test_large_host_scans_leave_no_buffer():
+    """A host-memory scan of few points whose partials take 134 MB frees them."""
+    print("large host scan", flush=True)
+    new = _new_buffers(
+        "import ctypes\n"
+        "sp = spec(100000, 65536, 'fp32')\n"
+        "assert zmc.plan(sp)['workspace_bytes'] > 100 << 20\n"
+        "f, s = zmc.scan_chunked(sp)\n"
+        "g, t = zmc.scan_range(sp, 0, 1000)\n"
+        "assert np.array_equal(f[:1000], g) and np.array_equal(s[:1000], t) and np.all(np.isfinite(f))\n")
+    assert len(new) == 1 and int(new[0].split("new ")[1].split("-byte")[0]) <= 8 << 20, new  # the range's own
