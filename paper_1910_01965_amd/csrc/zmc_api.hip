@@ -251,8 +251,9 @@ zmc_status make_plan(const zmc_scan_desc* d, uint64_t G, const zmc_launch_opts* 
       if (splits > cap) splits = cap;
     }
     if (splits < 1) splits = 1;
-    while (splits > 1 && 16.0 * (double)splits * (double)G > (double)kMaxWorkspace) splits /= 2;
   }
+  if (!(o && o->splits > 0))
+    while (splits > 1 && 16.0 * (double)splits * (double)G > (double)kMaxWorkspace) splits /= 2;
   // a sample-major piece that gives no lane a second group leaves the lanes past
   // it idle: only the waves that have work are launched (the same lanes take the
   // same groups)
