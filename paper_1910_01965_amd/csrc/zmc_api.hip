@@ -521,7 +521,7 @@ zmc_status zmc_scan_device_ex(const zmc_scan_desc* desc, const double* d_axis_va
   if (st != ZMC_OK) return st;
   zmc::UserKernels uk;
   if (desc->family == ZMC_USER) {
-    st = zmc::user_kernels(desc->integrand, desc->precision, desc->N, desc->M, &uk);
+    st = zmc::user_kernels(desc->integrand, desc->precision, desc->N, desc->M, &uk, pl.block);
     if (st != ZMC_OK) return st;
   }
   int dev = 0, stream_dev = 0;

@@ -80,7 +80,8 @@ hipError_t launch_rate_probe(int32_t op, int32_t blocks, int64_t iters, uint64_t
 struct UserKernels {
   hipFunction_t pm = nullptr, sm = nullptr, sm_big = nullptr, values = nullptr, batch = nullptr;
 };
-zmc_status user_kernels(const zmc_integrand* h, int precision, int N, int M, UserKernels* out);
+// `block`: the threads of the plan's blocks (above 256: one kernel more).
+zmc_status user_kernels(const zmc_integrand* h, int precision, int N, int M, UserKernels* out, int block = 256);
 hipError_t launch_user_scan(const UserKernels& k, const ScanParams& p, const Plan& plan,
                             hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end);
 hipError_t launch_user_values(const UserKernels& k, const ScanParams& p, uint64_t g, uint64_t s0,

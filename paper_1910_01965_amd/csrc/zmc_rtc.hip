@@ -40,10 +40,12 @@ constexpr size_t kMaxLogInError = 4000;
 
 struct Loaded {
   hipModule_t module = nullptr;
-  hipFunction_t pm = nullptr, sm = nullptr, sm_big = nullptr, values = nullptr, batch = nullptr;
+  hipFunction_t pm = nullptr, sm = nullptr, values = nullptr, batch = nullptr;
 };
 
-std::string program_text(const std::string& user, int precision, int N, int M) {
+// The kernels of one variant; `big`: the sample-major kernel for blocks of more than
+// 256 threads alone.
+std::string program_text(const std::string& user, int precision, int N, int M, bool big) {
   const char* T = precision == ZMC_FP64 ? "double" : "float";
   std::string s;
   s += "#include \"zmc_scan.hpp\"\n";
@@ -52,17 +54,16 @@ std::string program_text(const std::string& user, int precision, int N, int M) {
   s += "\n#line 1 \"zmc_user_kernels\"\n#include \"zmc_user.hpp\"\n";
   const std::string fam = std::string("zmc::UserFamily<") + T + ", " + std::to_string(N) + ", " +
                           std::to_string(M) + ">, " + T + ", " + std::to_string(N);
-  s += "extern \"C\" __global__ __launch_bounds__(256) void zmc_user_point_major(zmc::ScanParams p) {\n";
-  s += "  zmc::point_major_body<" + fam + ">(p);\n}\n";
   // sample-major blocks of up to 256 threads (every automatic plan and all of
   // N > 8), and of up to 1024 for explicit plans, whose bound of 128 VGPRs a lane
-  // can make FP64 integrands spill
-  for (const char* big : {"", "_1024"}) {
-    if (*big && N > zmc::kAnyMaxDims) continue;
-    s += std::string("extern \"C\" __global__ __launch_bounds__(") + (*big ? "1024" : "256") +
-         ") void zmc_user_sample_major" + big + "(zmc::ScanParams p) {\n";
-    s += "  __shared__ double lds[zmc::kSmLds];\n  zmc::sample_major_body<" + fam + ">(p, lds);\n}\n";
-  }
+  // can make FP64 integrands spill: that kernel is built when a plan asks for it,
+  // since each kernel is a fifth of a variant's build time
+  s += std::string("extern \"C\" __global__ __launch_bounds__(") + (big ? "1024" : "256") +
+       ") void zmc_user_sample_major(zmc::ScanParams p) {\n";
+  s += "  __shared__ double lds[zmc::kSmLds];\n  zmc::sample_major_body<" + fam + ">(p, lds);\n}\n";
+  if (big) return s;
+  s += "extern \"C\" __global__ __launch_bounds__(256) void zmc_user_point_major(zmc::ScanParams p) {\n";
+  s += "  zmc::point_major_body<" + fam + ">(p);\n}\n";
   s += "extern \"C\" __global__ __launch_bounds__(256) void zmc_user_values(zmc::ScanParams p, "
        "uint64_t g, uint64_t s0, int64_t count, double* out) {\n";
   s += "  zmc::debug_values_body<" + fam + ">(p, g, s0, count, out);\n}\n";
@@ -81,18 +82,18 @@ struct zmc_integrand {
   uint32_t flags = 0;  // ZMC_INTEGRAND_* bits
   std::mutex mu;
   std::string log;
-  std::map<std::tuple<int, int, int>, std::vector<char>> code;      // (precision, N, M)
-  std::map<std::tuple<int, int, int, int>, Loaded> loaded;          // (device, precision, N, M)
+  std::map<std::tuple<int, int, int, bool>, std::vector<char>> code;  // (precision, N, M, big)
+  std::map<std::tuple<int, int, int, int, bool>, Loaded> loaded;      // (device, precision, N, M, big)
 };
 
 namespace {
 
 // Compiles one variant into h->code; the caller holds h->mu.
-zmc_status compile_variant(zmc_integrand* h, int precision, int N, int M) {
+zmc_status compile_variant(zmc_integrand* h, int precision, int N, int M, bool big = false) {
   zmc::TraceRange trace_range("zmc_integrand compile");
-  const auto key = std::make_tuple(precision, N, M);
+  const auto key = std::make_tuple(precision, N, M, big);
   if (h->code.count(key)) return ZMC_OK;
-  const std::string text = program_text(h->source, precision, N, M);
+  const std::string text = program_text(h->source, precision, N, M, big);
   const auto t0 = std::chrono::steady_clock::now();
   hiprtcProgram prog = nullptr;
   hiprtcResult r = hiprtcCreateProgram(&prog, text.c_str(), "zmc_user.hip", kRtcHeaderCount,
@@ -125,37 +126,27 @@ zmc_status compile_variant(zmc_integrand* h, int precision, int N, int M) {
     r = hiprtcGetCode(prog, co.data());
   }
   (void)hiprtcDestroyProgram(&prog);
-  zmc::log(1, "user integrand: compiled the (precision %d, N = %d, M = %d) variant in %.2f s",
-           precision, N, M,
+  zmc::log(1, "user integrand: compiled the (precision %d, N = %d, M = %d)%s variant in %.2f s",
+           precision, N, M, big ? " large-block" : "",
            std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
   if (r != HIPRTC_SUCCESS) return fail(ZMC_E_DEVICE, "hiprtcGetCode: %s", hiprtcGetErrorString(r));
   h->code[key] = std::move(co);
   return ZMC_OK;
 }
 
-}  // namespace
-
-namespace zmc {
-
-zmc_status user_kernels(const zmc_integrand* hc, int precision, int N, int M, UserKernels* out) {
-  zmc_integrand* h = const_cast<zmc_integrand*>(hc);
-  std::lock_guard<std::mutex> lk(h->mu);
-  zmc_status st = compile_variant(h, precision, N, M);
+// Compiles and loads one variant on the current device; the caller holds h->mu.
+zmc_status load_variant(zmc_integrand* h, int dev, int precision, int N, int M, bool big, Loaded* out) {
+  const zmc_status st = compile_variant(h, precision, N, M, big);
   if (st != ZMC_OK) return st;
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return fail(ZMC_E_DEVICE, "hipGetDevice: %s", hipGetErrorString(e));
-  Loaded& L = h->loaded[std::make_tuple(dev, precision, N, M)];
+  Loaded& L = h->loaded[std::make_tuple(dev, precision, N, M, big)];
   if (L.module == nullptr) {
-    const std::vector<char>& co = h->code[std::make_tuple(precision, N, M)];
+    const std::vector<char>& co = h->code[std::make_tuple(precision, N, M, big)];
     hipModule_t mod = nullptr;
-    e = hipModuleLoadData(&mod, co.data());
-    if (e == hipSuccess) e = hipModuleGetFunction(&L.pm, mod, "zmc_user_point_major");
+    hipError_t e = hipModuleLoadData(&mod, co.data());
     if (e == hipSuccess) e = hipModuleGetFunction(&L.sm, mod, "zmc_user_sample_major");
-    if (e == hipSuccess && N <= zmc::kAnyMaxDims)
-      e = hipModuleGetFunction(&L.sm_big, mod, "zmc_user_sample_major_1024");
-    if (e == hipSuccess) e = hipModuleGetFunction(&L.values, mod, "zmc_user_values");
-    if (e == hipSuccess) e = hipModuleGetFunction(&L.batch, mod, "zmc_user_batch");
+    if (e == hipSuccess && !big) e = hipModuleGetFunction(&L.pm, mod, "zmc_user_point_major");
+    if (e == hipSuccess && !big) e = hipModuleGetFunction(&L.values, mod, "zmc_user_values");
+    if (e == hipSuccess && !big) e = hipModuleGetFunction(&L.batch, mod, "zmc_user_batch");
     if (e != hipSuccess) {
       if (mod != nullptr) (void)hipModuleUnload(mod);
       L = Loaded{};
@@ -163,9 +154,27 @@ zmc_status user_kernels(const zmc_integrand* hc, int precision, int N, int M, Us
     }
     L.module = mod;
   }
+  *out = L;
+  return ZMC_OK;
+}
+
+}  // namespace
+
+namespace zmc {
+
+zmc_status user_kernels(const zmc_integrand* hc, int precision, int N, int M, UserKernels* out, int block) {
+  zmc_integrand* h = const_cast<zmc_integrand*>(hc);
+  std::lock_guard<std::mutex> lk(h->mu);
+  int dev = 0;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return fail(ZMC_E_DEVICE, "hipGetDevice: %s", hipGetErrorString(e));
+  Loaded L, B;
+  zmc_status st = load_variant(h, dev, precision, N, M, false, &L);
+  if (st == ZMC_OK && block > 256) st = load_variant(h, dev, precision, N, M, true, &B);
+  if (st != ZMC_OK) return st;
   out->pm = L.pm;
   out->sm = L.sm;
-  out->sm_big = L.sm_big;
+  out->sm_big = B.sm;
   out->values = L.values;
   out->batch = L.batch;
   return ok();
@@ -189,7 +198,7 @@ hipError_t launch_user_scan(const UserKernels& k, const ScanParams& p, const Pla
   ScanParams arg = p;
   void* args[] = {&arg};
   const hipFunction_t f = plan.mode == ZMC_MODE_POINT_MAJOR ? k.pm : plan.block > 256 ? k.sm_big : k.sm;
-  if (f == nullptr) return hipErrorInvalidValue;  // the planner refuses such blocks
+  if (f == nullptr) return hipErrorInvalidValue;  // user_kernels was not told of such a block
   if (e == hipSuccess)
     e = hipModuleLaunchKernel(f, (unsigned)plan.grid_x, (unsigned)plan.splits, 1, (unsigned)plan.block,
                               1, 1, 0, stream, args, nullptr);
