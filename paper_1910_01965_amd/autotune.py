@@ -4,7 +4,10 @@ For every kernel variant (family, precision, N) the tuner times the batch
 path on that variant's scans of the 512-scan batch shape generator (sample
 counts capped to keep a sweep short) with candidate point-major tile lengths,
 and on small grids it times point-major against sample-major tiles to find
-the grid size where point-major starts to win.  The fastest candidate wins;
+the grid size where point-major starts to win.  Explicit tile lengths
+(pm_groups, sm_groups) are run as they are, without the planner's own cut of FP64
+grids and its sample-major tiles of several points, so the second comparison
+passes none where the planner would change them.  The fastest candidate wins;
 ties within 1% go to the longer tile (fewer split partials).  Output lines:
 
     family precision N pm_groups sm_groups pm_min_points
@@ -69,12 +72,13 @@ def tune_pm_min(zmc, family, precision, N, pm_groups, reps, log):
     from . import workloads as wl
     choice = 2 * PM_MIN_CANDIDATES[-1]
     M = wl.family_shape(family, N, 2, 4, 0, precision).M
+    # FP64 grids of these sizes are cut finer than the table's tiles
+    pm_opts = dict(pm_groups=pm_groups) if precision == "fp32" else {}
     for G in PM_MIN_CANDIDATES:
         L = max(2, int(round(G ** (1.0 / M))))
         sp = wl.family_shape(family, N, L, 1 << 14, 7, precision)
-        t_pm = _time_batch(zmc, [sp], reps, pm_groups=pm_groups, pm_min_points=1)
-        t_sm = _time_batch(zmc, [sp], reps, pm_groups=pm_groups, pm_min_points=1 << 40,
-                           sm_groups=SM_GROUPS)
+        t_pm = _time_batch(zmc, [sp], reps, pm_min_points=1, **pm_opts)
+        t_sm = _time_batch(zmc, [sp], reps, pm_min_points=1 << 40)  # the table's sm_groups
         log(f"    G={sp.G}: point-major {t_pm * 1e3:.2f} ms, sample-major {t_sm * 1e3:.2f} ms")
         if t_pm <= t_sm:
             choice = sp.G
