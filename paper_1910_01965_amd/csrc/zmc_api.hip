@@ -323,6 +323,7 @@ void fill_params(const zmc_scan_desc* d, uint64_t G, const zmc::Plan& pl, const 
     vol *= d->hi[k] - d->lo[k];
   }
   p->vol = vol;
+  if (d->family == ZMC_SIN_SUM && d->precision == ZMC_FP64) zmc::fold_sin_box(d->N, p->lo, p->hi);
   p->n_params = d->family == ZMC_USER ? d->n_params : 0;
   for (int i = 0; i < p->n_params; ++i) p->params[i] = d->params[i];
   p->axis = d_axis;

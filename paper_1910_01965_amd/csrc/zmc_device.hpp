@@ -464,6 +464,7 @@ constexpr double kLog2e = 1.4426950408889634074;
 // (for |r| >= 2^23 an FP32 phase no longer resolves a revolution and the
 // reduced phase is 0).
 constexpr double kInv2Pi = 0.15915494309189533577;
+constexpr double kPi = 3.14159265358979323846;
 constexpr double kInv2PiLo = -9.839338337591243e-18;  // 1/(2 pi) - kInv2Pi
 
 __device__ __forceinline__ float sin_turns(float r) {
@@ -587,6 +588,53 @@ __host__ __device__ __forceinline__ double cos_turns(double r) {
   return sin_2pi_quarter(0.25 - __builtin_fabs(t));
 }
 
+// sin(s) in FP64, s in radians below 2^51: with c = 1 / pi, n = rint(s c), by adding
+// kRoundMagic, and u = s c - n with one rounding, at u's own magnitude, so that neither a
+// small phase nor a reduced one carries the rounding of the whole (a product rounded
+// before its reduction has 5 to 20 % more error on boxes of 1 to 10); then (-1)^n
+// sin(pi u) with the quarter-turn polynomial's coefficients scaled by powers of two.
+// n's parity is the low bit of s c + kRoundMagic, shifted into the sign.
+__host__ __device__ __forceinline__ double sin_radians(double s) {
+  constexpr double c = 2.0 * kInv2Pi;
+  const double m = __builtin_fma(s, c, kRoundMagic);
+  const double u = __builtin_fma(s, c, -(m - kRoundMagic));
+  const double u2 = u * u;
+  double p = 0.10071467531221244 * 0x1p-17;
+  p = __builtin_fma(p, u2, -0.7176853699001249 * 0x1p-15);
+  p = __builtin_fma(p, u2, 3.8199227975201033 * 0x1p-13);
+  p = __builtin_fma(p, u2, -15.094641368684599 * 0x1p-11);
+  p = __builtin_fma(p, u2, 42.05869391526577 * 0x1p-9);
+  p = __builtin_fma(p, u2, -76.70585975263434 * 0x1p-7);
+  p = __builtin_fma(p, u2, 81.60524927607172 * 0x1p-5);
+  p = __builtin_fma(p, u2, -41.34170224039975 * 0x1p-3);
+  p = __builtin_fma(p, u2, 6.283185307179586 * 0x1p-1);
+  const uint64_t odd = __builtin_bit_cast(uint64_t, m) << 63;
+  return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, u * p) ^ odd);
+}
+
+// r less whole turns, in radians.  The product is rounded before its reduction: fused
+// with it, its rounding error, of any size for a large r, would be the result.
+__host__ __device__ inline double fold_turns(double r) {
+#pragma clang fp contract(off)
+  const double h = r * kInv2Pi;
+  return (h - __builtin_rint(h)) * (2.0 * kPi);
+}
+
+// Phases of 2^48 and more, of which FP64 resolves a few hundredths of a turn and less:
+// a box that reaches them is replaced by one whose map y = A t + B has A and B modulo
+// 2 pi (t is a whole number), which keeps the phases that sin_radians gets below 2^50.
+// On the host, once per scan.
+inline void fold_sin_box(int N, double* lo, double* hi) {
+  double reach = 0.0;
+  for (int k = 0; k < N; ++k) reach += __builtin_fmax(__builtin_fabs(lo[k]), __builtin_fabs(hi[k]));
+  if (reach < 0x1p48) return;
+  for (int k = 0; k < N; ++k) {
+    const double h = hi[k] - lo[k], a = fold_turns(h * 0x1p-32), b = fold_turns(lo[k] + h * 0x1p-33);
+    lo[k] = b - 0.5 * a;
+    hi[k] = lo[k] + a * 0x1p32;
+  }
+}
+
 // Radians to a fraction of a revolution in [-1/2, 1/2], without the rounding of
 // the whole revolutions: |error| below 2^-54 plus 2^-106 |s| (host checks of the
 // phase reductions).
@@ -644,15 +692,16 @@ struct ParamCursor {
 // ---------------------------------------------------------------------------
 
 // sin(sum_l x_l + sum_k y_k): the paper's test integrand, Eq. (2) and Eq. (4).
-// FP64: the phase is summed coordinate by coordinate, as the formula states it
-// (folding the box offsets into the point's constant moves its roundings by up
-// to 3e-15), and reduced as it is: a quarter turn taken off first, for a cosine
-// without the sine's fold, rounds a phase of w radians to 2^-55 of a revolution,
-// a relative error of 2e-16 / w in f (1.0, f = 0, on a box of 1e-17).
+// FP64: the phase is summed in radians, coordinate by coordinate, as the formula
+// states it (folding the box offsets into the point's constant, or carrying the
+// coordinates in turns, adds up to 60 % to its error), and reduced as it is: a
+// quarter turn taken off first, for a cosine without the sine's parity, rounds a
+// phase of w radians to 2^-55 of a revolution, a relative error of 2e-16 / w in f (1.0,
+// f = 0, on a box of 1e-17).  Boxes that reach 2^48 come folded (fold_sin_box).
 template <typename T, int N> struct SinSum {
   static constexpr int kMinDims = 1;
   T A[N], B[N];
-  T sx;        // FP64: sum of x; FP32: sum x + sum B (all in revolutions)
+  T sx;        // FP64: sum of x; FP32: sum x + sum B (A and sx in revolutions)
   __host__ __device__ void setup(const ScanParams& p, uint64_t g) {
     double s = 0.0, sb = 0.0;
     ParamCursor x(p, g);
@@ -661,18 +710,21 @@ template <typename T, int N> struct SinSum {
     for (int k = 0; k < N; ++k) {
       double a, b;
       Unif<T>::affine(p.lo[k], p.hi[k], &a, &b);
-      A[k] = (T)(a * kInv2Pi);
-      B[k] = (T)(b * kInv2Pi);
+      A[k] = sizeof(T) == 8 ? (T)a : (T)(a * kInv2Pi);
+      B[k] = (T)b;
       sb += b;
     }
-    sx = sizeof(T) == 8 ? (T)(s * kInv2Pi) : (T)((s + sb) * kInv2Pi);
+    if constexpr (sizeof(T) == 8)
+      sx = __builtin_fabs(s) < 0x1p48 ? s : fold_turns(s);
+    else
+      sx = (T)((s + sb) * kInv2Pi);
   }
   __host__ __device__ __forceinline__ T value(const T* t) const {
     if constexpr (sizeof(T) == 8) {
       double sy = fmaT(A[0], t[0], B[0]);
 #pragma unroll
       for (int k = 1; k < N; ++k) sy += fmaT(A[k], t[k], B[k]);
-      return sin_turns(sx + sy);
+      return sin_radians(sx + sy);
     } else {
       float ph = sx;
 #pragma unroll

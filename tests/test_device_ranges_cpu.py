@@ -37,3 +37,11 @@ def test_cosexp_exponent_and_phase_over_their_ranges(tmp_path):
     2^t of an exponent that overflows as exp gives it."""
     e, c, bad = _run("cosexp_ranges", tmp_path)
     assert float(e) < 1.0 and float(c) < 1.0 and int(bad) == 0, (e, c, bad)
+
+
+def test_sin_phases_are_reduced_without_the_rounding_of_the_whole(tmp_path):
+    """No more error than one rounding of the sum and one of the reduced phase allow, none
+    more than with the product rounded first (up to the noise of 20000 samples), and
+    bounded values at phases of any size."""
+    worst, ratio, out, flat = _run("sin_phases", tmp_path)
+    assert float(worst) < 1.0 and float(ratio) < 1.02 and int(out) == 0 and int(flat) == 0, (worst, ratio, out, flat)

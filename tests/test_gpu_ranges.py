@@ -69,3 +69,19 @@ def test_means_near_the_largest_double(samples):
     for i, (f, s) in enumerate(runs):
         print("large means", samples, i, flush=True)
         assert f.cpu().tolist() == [1e306, -1.7e308] and s.cpu().tolist() == [0.0, 0.0]
+
+
+# phases that FP64 no longer resolves: bounded values, spread like a sine's
+@pytest.mark.parametrize("box,x", [(1e15, 0.5), (1e18, 0.5), (1.0, 1e17), (1e300, 1e300)])
+def test_sin_of_unresolved_phases_stays_bounded(box, x):
+    import torch
+    from paper_1910_01965_amd import zmc
+    spec = wl.ScanSpec("sin_sum", [x * np.linspace(1.0, 1.5, 70)], np.zeros(2), np.array([box, 1.0]), 4099, 5, "fp64")
+    for mode in ("point_major", "sample_major"):
+        print("unresolved phases", box, x, mode, flush=True)
+        f, s = zmc.scan(spec, mode=mode)
+        torch.cuda.synchronize()
+        f, s = f.cpu().numpy() / box, s.cpu().numpy() / box * np.sqrt(4099)
+        assert np.all(np.abs(f) <= 1.0) and np.all(np.isfinite(s)) and np.all(s <= 1.0)
+        if 1.0 < box < 1e20:
+            assert np.all(np.abs(f) < 0.07) and np.all(np.abs(s - 0.5 ** 0.5) < 0.05)
