@@ -27,10 +27,12 @@ constexpr int kMinWaves = sizeof(T) == 4 ? (kTwoForms<Fam> && N > kAnyMaxDims ? 
 // Batch kernels hold the point-major and the sample-major loops.  FP32 at 5, 4 and 3:
 // 12 scans of 600 to 1000 points, N = 8, 119 : 100 : 100 for the Gaussian and 113 : 100 :
 // 103 for SIN_SUM, 4 scans of 40000 points 128 : 100 : 113 and 104 : 100 : 118; N = 16
-// Gaussian 206 : 100 : 77.  FP64 at 4 against 3: COSEXP N = 8 121 : 100, N = 7 97 : 100; at 3
+// Gaussian 206 : 100 : 77.  Five stay for N = 7, where small scans would gain 11 % and
+// large ones lose 3 % (a batch of 512 scans: 5.80 s, 5.84 with four from N = 7 on, 5.75
+// with five up to N = 8).  FP64 at 4 against 3: COSEXP N = 8 121 : 100, N = 7 97 : 100; at 3
 // against 2: N = 16 118 to 137 : 100 in small scans, 85 to 93 : 100 in large ones.
 template <class Fam, typename T, int N>
-constexpr int kBatchWaves = sizeof(T) == 4 ? (N <= 6 ? 5 : kTwoForms<Fam> && N == 16 ? 3 : 4)
+constexpr int kBatchWaves = sizeof(T) == 4 ? (N <= (kTwoForms<Fam> ? 6 : 7) ? 5 : kTwoForms<Fam> && N == 16 ? 3 : 4)
                                            : (N < kAnyMaxDims ? 4 : N < 16 ? 3 : 2);
 
 template <class Fam, typename T, int N>
