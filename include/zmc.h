@@ -303,7 +303,8 @@ zmc_status zmc_debug_values(const zmc_scan_desc* desc, const double* d_axis_vals
  * zmc_integrand_create copies the source and compiles one small variant to
  * report errors (ZMC_E_INVALID with the compiler's log in zmc_last_error);
  * every (precision, N, M) variant a scan needs is then compiled on first use
- * (a few seconds) and kept, and loaded once per device.  It needs no GPU.
+ * (a few seconds; one kernel more for explicit blocks of more than 256 threads)
+ * and kept, and loaded once per device.  It needs no GPU.
  * The handle may be shared by threads.  zmc_integrand_destroy waits for
  * each device it was loaded on to go idle before unloading its kernels.
  * ZMC_USER scans run through every entry point: single scans, chunked
@@ -427,7 +428,9 @@ const char* zmc_tune_source(void);
  * so requests that arrive while others are on the GPU join the next slice
  * and their work overlaps on the device.  A request completes when its last
  * tile and its split merge have run; its latency is completion minus submit
- * time.  Requests that can never fit the budget fail with ZMC_E_NOMEM.
+ * time.  Requests that can never fit the budget fail with ZMC_E_NOMEM (FP64
+ * requests count with the pieces of the tuned table where their finer ones do
+ * not fit the whole budget: up to 8 MiB of partials then lie above it).
  * ---------------------------------------------------------------------- */
 typedef struct zmc_server zmc_server;
 
