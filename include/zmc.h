@@ -177,7 +177,7 @@ zmc_status zmc_scan(const zmc_scan_desc* desc, double* f, double* sigma);
  * memory), and with both pointers NULL too.
  * Split partials, when the plan needs them (16 B per point and sample
  * piece; zmc_plan tells: plans with several pieces, among them those of many short
- * FP64 scans of 64 to 65535 points on 256 compute units), come from a per-device
+ * FP64 scans of 64 to 65536 points on 256 compute units), come from a per-device
  * cache of at most 16 buffers of 1 to 8 MiB and four of 16 to 256 MiB, in
  * power-of-two sizes, held by the library until the process ends and reused
  * without a host wait (a buffer still in use by another call's kernels is

@@ -181,7 +181,7 @@ constexpr uint64_t kDefaultChunk = (uint64_t)1 << 24;  // points per chunk of a 
 constexpr uint64_t kMaxBytes = (uint64_t)1 << 56;
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// FP64 grids that do not fill the device with one wave per 64 points: the
+// FP64 grids that fill the device with one wave per 64 points at most: the
 // number of sample pieces with which the point-major layout is expected to be
 // faster than the sample-major one, or 0.  Point-major pays once per wave and
 // piece (set-up, moments, a share of the merge pass: about 6 groups of four
@@ -193,15 +193,19 @@ size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 // Measured (sample- -> point-major, back-to-back calls): 20467 points x 2049
 // samples N = 12 319 -> 183 us, 40000 x 257 N = 4 121 -> 32, 30000 x 1024 N = 8
 // 234 -> 107, 15000 x 2050 N = 2 84 -> 50; 500 x 16384 N = 4 stays sample-major
-// (its kernel takes 23 us, point-major 24 and the merge).  The FP32 path keeps the
+// (its kernel takes 23 us, point-major 24 and the merge).  Grids of just one wave per
+// SIMD are point-major anyway, but a lone wave gains nothing from the issue phases: 65536
+// points of COSEXP, N = 2, in 1 and 5 pieces at 500 samples 83 -> 70 us, in 4 at 256 49 -> 45,
+// in 2 at 128 28 -> 31, which stay in one (unphased 69, 42 and 25).  The FP32 path keeps the
 // sample-major layout for such grids: its sums are shifted by a lane's first
 // sample, so another layout moves a result by FP32 roundings.
 uint64_t mid_grid_pieces(uint64_t G, uint64_t groups, int N, uint64_t simds) {
-  if (G < 64 || G >= simds * 64) return 0;
+  if (G < 64 || G > simds * 64) return 0;
   const uint64_t waves = cdiv(G, 64);
   uint64_t splits = cdiv(5 * simds, waves);
   splits = std::min<uint64_t>(splits, std::max<uint64_t>(1, groups / 16));
   splits = std::min<uint64_t>(splits, 256);
+  if (G == simds * 64 && splits < 3) return 0;
   auto per_simd = [&](uint64_t w) { return std::max(1.7, (double)w / (double)simds); };
   const double pm = ((double)cdiv(groups, splits) + 6.0) * per_simd(waves * splits) +
                     (splits > 1 ? 38.0 / N : 0.0);
